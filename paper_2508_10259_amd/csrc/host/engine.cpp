@@ -24,6 +24,16 @@ static const char* off(const void* p, size_t bytes) { return (const char*)p + by
 // to 8 rows (see norm_proj).
 static bool fused_norm(const Ctx& c, int rows) { return c.model->ct == DT_F16 && rows <= 8; }
 
+// fp32 passes of up to 64 tokens run gemv_f32, which applies the RMSNorm itself.
+static bool short_f32(const Model& md, int M) { return md.ct == DT_F32 && M <= 64; }
+
+// h += x W^T of such a pass, K split over more workgroups for long rows.
+static hipError_t resid_f32(const Ctx& c, const void* x, const void* W, int M, int K, float* h, hipStream_t s) {
+  const int d = c.model->cfg.d_model;
+  return gemv_f32(EPI_RESID, (const float*)x, false, 0.f, (const float*)W, M, d, K, h, d, s, f32_split(d, K), c.kpart(),
+                  c.wcnt());
+}
+
 // Above 8 rows the fp16 decode GEMVs use the wide GEMM (128 weight rows per
 // workgroup, activations staged in LDS) with split-K partial sums: at 16 rows
 // of the 7B model it decodes 4% faster than the skinny GEMV with separate lo
@@ -295,6 +305,7 @@ static hipError_t tokens_resid(Ctx& c, const void* x, const void* W, int M, int 
   const int d = md.cfg.d_model;
   const int splits = md.ct == DT_F16 ? prefill_ksplit(M, d, K) : 1;
   normed = false;
+  if (short_f32(md, M)) return resid_f32(c, x, W, M, K, c.h(), s);
   if (splits > 1) {
     hipError_t e = gemm_big_part(x, W, M, d, K, splits, c.kpart(), s);
     if (e == hipSuccess) e = resid_norm(c.kpart(), splits, M, d, c.h(), md.cfg.rms_eps, c.u(), s);
@@ -314,13 +325,17 @@ static hipError_t layer_tokens(Ctx& c, int l, int M, const Segs& sg, hipStream_t
   const Model& md = *c.model;
   const Cfg& m = md.cfg;
   const int d = m.d_model, F = m.d_ffn, dt = md.ct;
-  if (!u_ready) TRY(rmsnorm(dt, c.h(), M, d, m.rms_eps, c.u(), s));
+  const bool f32s = short_f32(md, M);  // the projections then normalise h themselves
+  if (!u_ready && !f32s) TRY(rmsnorm(dt, c.h(), M, d, m.rms_eps, c.u(), s));
   if (kv_fused) {  // the QKV GEMM's epilogue appends K/V (the token tables are the pass's)
     KvEpi kv{(const int64_t*)(c.ws + c.lay.tok_base), (const int32_t*)(c.ws + c.lay.tok_pos), c.kslab(l), c.vslab(l),
              c.rope(), d, m.head_dim};
     TRY(gemm_qkv_kv(c.u(), md.wqkv(l), M, d, c.qkv(), kv, s));
   } else {
-    TRY(gemm(dt, EPI_STORE, c.u(), md.wqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
+    if (f32s)
+      TRY(gemv_f32(EPI_STORE, c.h(), true, m.rms_eps, (const float*)md.wqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
+    else
+      TRY(gemm(dt, EPI_STORE, c.u(), md.wqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
     if (tables)  // each token's slot from the pass's tables (7B batch-64 extension: 19.05 -> 18.92 ms per step)
       TRY(kv_append_tab(c.qkv(), M, (const int64_t*)(c.ws + c.lay.tok_base), (const int32_t*)(c.ws + c.lay.tok_pos),
                         m.n_heads, m.head_dim, c.rope(), c.kslab(l), c.vslab(l), s));
@@ -330,8 +345,11 @@ static hipError_t layer_tokens(Ctx& c, int l, int M, const Segs& sg, hipStream_t
   TRY(attn_prefill(dt, c.qkv(), sg, m.n_heads, m.head_dim, c.pages(), c.rope(), c.kslab(l), c.vslab(l), c.o(),
                    s));
   TRY(tokens_resid(c, c.o(), md.wo(l), M, d, s, u_ready));
-  if (!u_ready) TRY(rmsnorm(dt, c.h(), M, d, m.rms_eps, c.u(), s));
-  TRY(gemm(dt, EPI_SWIGLU, c.u(), md.wgu(l), M, 2 * F, d, c.a(), F, s));
+  if (!u_ready && !f32s) TRY(rmsnorm(dt, c.h(), M, d, m.rms_eps, c.u(), s));
+  if (f32s)
+    TRY(gemv_f32(EPI_SWIGLU, c.h(), true, m.rms_eps, (const float*)md.wgu(l), M, 2 * F, d, (float*)c.a(), F, s));
+  else
+    TRY(gemm(dt, EPI_SWIGLU, c.u(), md.wgu(l), M, 2 * F, d, c.a(), F, s));
   TRY(tokens_resid(c, c.a(), md.wd(l), M, F, s, u_ready));
   return hipSuccess;
 }
@@ -464,7 +482,9 @@ static hipError_t norm_proj(const Rows& g, int epi, const float* h, const void* 
                             std::string& err, const float* ss = nullptr, QkvParts* defer = nullptr) {
   const Model& md = *g.c->model;
   const float eps = md.cfg.rms_eps;
-  if (fused_norm(*g.c, g.n)) {
+  if (short_f32(md, g.n)) {
+    TRY(gemv_f32(epi, h, true, eps, (const float*)W, g.n, N, K, (float*)out, ldo, s));
+  } else if (fused_norm(*g.c, g.n)) {
     TRY(gemv_rmsnorm(md.ct, epi, hhi, eps, W, g.n, N, K, out, ldo, s, hlo, nullptr, olo));
   } else {
     void* ulo = md.ct == DT_F16 ? g.hlo() : nullptr;
@@ -520,6 +540,7 @@ static hipError_t resid_proj(const Rows& g, const void* x, const void* xlo, cons
     if (e == hipSuccess) e = part_resid(c.kpart(), splits, g.n, d, g.h(), o16, olo, s, ss);
     return e;
   }
+  if (short_f32(md, g.n)) return resid_f32(c, x, W, g.n, K, g.h(), s);
   const int splits = md.ct == DT_F16 ? decode_ksplit(d, K) : 1;
   if (splits > 1) {
     hipError_t e = gemm_part(x, xlo, W, g.n, d, K, splits, c.kpart(), s);

@@ -105,7 +105,7 @@ struct CtxLayout {
   size_t order;  // the rows by decreasing length [B] int32 (decode attention dispatch order)
   size_t tok_base, tok_pos;  // a token pass's pool offsets [T] int64 and positions [T] int32 (K/V append)
   size_t ss;  // decode rows' sums of squares per 128 residual columns [B][d/128]
-  size_t wcnt;  // arrival counters of the wide decode GEMM's weight tiles (zero between launches)
+  size_t wcnt;  // arrival counters of the split-K GEMMs' weight tiles (zero between launches)
   // persistent decode (fp16, up to 8 rows): fp16 pairs [2][B][width] of h, the
   // attention output and the SwiGLU output, split-K partials, sync words
   size_t fx_hp, fx_op, fx_ap, fx_part, fx_sync;
@@ -223,6 +223,14 @@ inline size_t prefill_part_floats(const Cfg& c, int pass_tokens) {
   return best;
 }
 
+// K splits of an fp32 residual projection of up to 64 tokens (16-row strips,
+// one workgroup each): a strip's weights (64 K bytes) are kept to about 64 KB per
+// split while the splits' strips number at most 256, one per CU.  Merging the
+// splits costs a counter round trip (about 2 us), which shorter ranges do not repay.
+inline int f32_split(int N, int K) {
+  return std::max(1, std::min(K / 1024, 256 / std::max(N / 16, 1)));
+}
+
 inline int check_ctx_args(const Cfg& c, int batch, int capacity, int pass_tokens, std::string& err) {
   if (batch < 1 || batch > 1024) { err = "batch must be in [1, 1024]"; return S_EINVAL; }
   if (capacity < 64 || capacity % 64 != 0 || capacity > (1 << 20)) {
@@ -279,6 +287,7 @@ inline CtxLayout ctx_layout(const Cfg& c, int batch, int capacity, int pass_toke
                    decode_wsplit((int)NB, (int)d) * B * NB});
   }
   if (es == 2) kp = std::max(kp, prefill_part_floats(c, (int)x.pass_tokens));
+  else kp = std::max(kp, (size_t)std::max(f32_split((int)d, (int)d), f32_split((int)d, (int)F)) * std::min<size_t>(T, 64) * d);
   x.kpart = o; o = align256(o + kp * 4);
   x.part = o; o = align256(o + B * (size_t)c.n_heads * x.max_splits * (c.head_dim + 2) * 4);
   x.logits = o; o = align256(o + B * (size_t)bins_padded(c) * 4);
@@ -306,7 +315,7 @@ inline CtxLayout ctx_layout(const Cfg& c, int batch, int capacity, int pass_toke
   x.hk_keys = o; o = align256(o + (share ? B * (size_t)x.ppr * 8 : 0));
   x.hk_rows = o; o = align256(o + (share ? 2 * B * 8 : 0));
   x.xfer = o; o = align256(o + B * 16);
-  x.wcnt = o; o = align256(o + std::max({3 * d, 2 * F, (size_t)bins_padded(c), d}) / 128 * 4);
+  x.wcnt = o; o = align256(o + std::max({3 * d / 128, 2 * F / 128, (size_t)bins_padded(c) / 128, d / 16}) * 4);
   x.total = o;
   return x;
 }

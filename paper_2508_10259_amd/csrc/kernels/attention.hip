@@ -8,12 +8,12 @@
 //
 //  * k_kv_append:     new tokens of a pass -> rotate k (RoPE), write k and v
 //                     at their absolute positions.
-//  * k_attn_prefill_mfma (fp16) / k_attn_prefill (fp32): causal attention of
-//                     a pass's tokens (a row's new segment at positions
-//                     pos..pos+n-1) over keys 0..pos+n-1 of that row, K/V
-//                     tiles staged in LDS, online softmax; the fp16 kernel
-//                     runs both products on MFMA.  k_attn_extend (fp16) takes
-//                     passes whose segments are at most 16 tokens long.
+//  * k_attn_prefill_mfma (fp16) / k_attn_f32 (fp32): causal attention of a
+//                     pass's tokens (a row's new segment at positions
+//                     pos..pos+n-1) over keys 0..pos+n-1 of that row, online
+//                     softmax, both products on MFMA; the fp16 kernel stages
+//                     K/V tiles in LDS.  k_attn_extend (fp16) takes passes
+//                     whose segments are at most 16 tokens long.
 //  * k_attn_decode:   one query per row at position p = lens[b] + jpos (a
 //                     fed-back action token).  Appends its own K/V, then
 //                     each workgroup covers one split of the row's keys 0..p
@@ -175,99 +175,168 @@ hipError_t kv_append(int ct, const float* qkv, Segs sg, int H, int dh, KvPages k
 
 // ----------------------------------------------------------------------------
 
-template <typename T, int DH>
-__global__ __launch_bounds__(256) void k_attn_prefill(const float* __restrict__ qkv, const int32_t* __restrict__ row,
-                                                      const int32_t* __restrict__ pos,
-                                                      const int32_t* __restrict__ off, int H, KvPages kp,
-                                                      const float2* __restrict__ rope, const T* __restrict__ kslab,
-                                                      const T* __restrict__ vslab, T* __restrict__ o, float scale) {
-  constexpr int QT = 64, KT = 32, HALF = DH / 2, DPT = DH / 4;
-  __shared__ float Qs[QT][DH + 1];
-  __shared__ float Ks[KT][DH + 1];
-  __shared__ float Vs[KT][DH];
-  __shared__ float Ps[QT][KT + 1];
-  const int s = blockIdx.z, h = blockIdx.y, tid = threadIdx.x;
-  const int b = row[s], p0 = pos[s], t0 = off[s], n = off[s + 1] - off[s];
-  const int q_lo = blockIdx.x * QT;
+// fp32 attention of a pass's tokens on the fp32 matrix cores, for whole
+// prefixes and short extensions alike: a workgroup takes 16 queries of one
+// segment and head, its four waves every fourth block of 16 keys, each with
+// its own online softmax, merged in LDS at the end.
+//
+// Both products are computed transposed: S^T = K Q^T leaves lane (r, g) the
+// scores of query r with keys 4g .. 4g+3, which are the B operand of
+// O^T = V^T P^T as they stand (step i of the MFMA takes key 4g + i of every
+// lane group), so the weights never pass through LDS, and a query's maximum,
+// sum and rescaling factor live in the lanes that hold its output.  K and V
+// come straight from global memory, 16 bytes per lane: row j of V^T's block nb
+// is dimension 4j + nb, so one load of 4 consecutive dimensions serves four
+// blocks.  Bound by the K/V loads' latency at the sizes measured (4 rows of
+// 200-400 tokens, 16 heads of 64: 136 -> 27 us per launch against FMA tiles of
+// 64 queries; 16 new tokens per row over the same prefixes 142 -> 15.5 us).
+template <int DH>
+__global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ qkv, const int32_t* __restrict__ row,
+                                                  const int32_t* __restrict__ pos, const int32_t* __restrict__ off,
+                                                  int H, KvPages kp, const float2* __restrict__ rope,
+                                                  const float* __restrict__ kslab, const float* __restrict__ vslab,
+                                                  float* __restrict__ o, float scale,
+                                                  const int32_t* __restrict__ order) {
+  constexpr int NS = DH / 16, HALF = DH / 2, NH = DH / 64, LDO = DH + 4;
+  __shared__ float wm[4][16], wl[4][16];
+  __shared__ __attribute__((aligned(16))) float wo[4][16][LDO];
+  const int sg = order ? __builtin_amdgcn_readfirstlane(order[blockIdx.z]) : (int)blockIdx.z;
+  const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4;
+  const int b = row[sg], p0 = pos[sg], t0 = off[sg], n = off[sg + 1] - off[sg];
+  const int q_lo = blockIdx.x * 16;
   if (q_lo >= n) return;  // uniform across the workgroup
   const int d = H * DH;
+  const int kv_end = p0 + (n < q_lo + 16 ? n : q_lo + 16);  // exclusive
 
-  for (int e = tid; e < QT * HALF; e += blockDim.x) {
-    const int qi = e / HALF, ii = e % HALF;
-    float x0 = 0.f, x1 = 0.f;
-    if (q_lo + qi < n) {
-      const int tok = t0 + q_lo + qi, p = p0 + q_lo + qi;
-      const float* q = qkv + (size_t)tok * 3 * d + h * DH;
-      const float2 cs = rope[(size_t)p * HALF + ii];
-      const float a = q[ii], c = q[ii + HALF];
-      x0 = (a * cs.x - c * cs.y) * scale;
-      x1 = (a * cs.y + c * cs.x) * scale;
-    }
-    Qs[qi][ii] = x0;
-    Qs[qi][ii + HALF] = x1;
-  }
-
-  const int qi = tid >> 2, sub = tid & 3;
-  const bool valid = q_lo + qi < n;
-  const int qpos = valid ? p0 + q_lo + qi : -1;
-  const int kv_end = p0 + (n < q_lo + QT ? n : q_lo + QT);  // exclusive
-  float m = -INFINITY, l = 0.f, acc[DPT];
+  float4 kx[NS], vx[4][NH];
+  auto load = [&](int kb, float4 (&k)[NS], float4 (&v)[4][NH]) __attribute__((always_inline)) {
+    // 16 keys from a multiple of 16 lie in one page; slots past the last key exist
+    // but may hold anything: their scores are masked, their values zeroed
+    const size_t pb = kv_slot(kv_page_u(kp, b, kb), H, h, 0, DH);
+    const float* Kb = kslab + pb + (size_t)((kb + r) & (KV_PAGE - 1)) * DH + 4 * g;
 #pragma unroll
-  for (int i = 0; i < DPT; ++i) acc[i] = 0.f;
-
-  for (int k0 = 0; k0 < kv_end; k0 += KT) {
-    __syncthreads();  // Qs ready on the first pass; Ks/Vs/Ps free on later ones
-    const size_t tb = kv_slot(kv_page(kp, b, k0), H, h, k0 & (KV_PAGE - 1), DH);  // the tile lies in one page
-    for (int e = tid; e < KT * DH; e += blockDim.x) {
-      const int kk = e / DH, dd = e % DH;
-      const bool ok = k0 + kk < kv_end;
-      Ks[kk][dd] = ok ? ld<T>(kslab, tb + (size_t)kk * DH + dd) : 0.f;
-      Vs[kk][dd] = ok ? ld<T>(vslab, tb + (size_t)kk * DH + dd) : 0.f;
-    }
-    __syncthreads();
-    float sc[KT / 4];
-    float mx = -INFINITY;
+    for (int s = 0; s < NS; ++s) k[s] = *(const float4*)(Kb + 16 * s);
 #pragma unroll
-    for (int jj = 0; jj < KT / 4; ++jj) {
-      const int kk = sub + 4 * jj, kp = k0 + kk;
-      float t = -INFINITY;
-      if (kp <= qpos && kp < kv_end) {
-        t = 0.f;
-#pragma unroll 16
-        for (int dd = 0; dd < DH; ++dd) t = fmaf(Qs[qi][dd], Ks[kk][dd], t);
+    for (int i = 0; i < 4; ++i) {
+      const int key = kb + 4 * g + i;
+      const float* Vb = vslab + pb + (size_t)(key & (KV_PAGE - 1)) * DH + 4 * r;
+      const bool ok = key < kv_end;
+#pragma unroll
+      for (int x = 0; x < NH; ++x) {
+        const float4 t = *(const float4*)(Vb + 64 * x);
+        v[i][x] = float4{ok ? t.x : 0.f, ok ? t.y : 0.f, ok ? t.z : 0.f, ok ? t.w : 0.f};
       }
-      sc[jj] = t;
-      mx = fmaxf(mx, t);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
+  };
+  int kb = wave * 16;
+  if (kb < kv_end) load(kb, kx, vx);
+
+  // this lane's query r: dims 16s + 4g + e, rotated and scaled (rows past the
+  // segment read its first query; their scores are masked, their output unused)
+  const int qi = q_lo + r < n ? q_lo + r : q_lo;
+  const int qpos = p0 + qi;
+  float qf[NS][4];
+  {
+    const float* q = qkv + (size_t)(t0 + qi) * 3 * d + h * DH + 4 * g;
+    const float2* rp = rope + (size_t)qpos * HALF + 4 * g;
+#pragma unroll
+    for (int s = 0; s < NS / 2; ++s) {
+      const float4 a = *(const float4*)(q + 16 * s), c = *(const float4*)(q + 16 * s + HALF);
+      const float4 r0 = *(const float4*)(rp + 16 * s), r1 = *(const float4*)(rp + 16 * s + 2);
+      const float av[4] = {a.x, a.y, a.z, a.w}, cv[4] = {c.x, c.y, c.z, c.w};
+      const float cx[4] = {r0.x, r0.z, r1.x, r1.z}, cy[4] = {r0.y, r0.w, r1.y, r1.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        qf[s][e] = (av[e] * cx[e] - cv[e] * cy[e]) * scale;
+        qf[s + NS / 2][e] = (av[e] * cy[e] + cv[e] * cx[e]) * scale;
+      }
+    }
+  }
+  auto el = [](const float4& v, int e) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; };
+
+  float m = -INFINITY, l = 0.f;
+  f32x4 acc[NS];  // block 4x + nb: dims 64x + 4 row + nb of query r
+#pragma unroll
+  for (int j = 0; j < NS; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (; kb < kv_end; kb += 64) {
+    float4 kn[NS], vn[4][NH];
+    const bool more = kb + 64 < kv_end;
+    if (more) load(kb + 64, kn, vn);  // in flight while this block computes
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+    for (int s = 0; s < NS; s += 2)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(el(kx[s], e), qf[s][e], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(el(kx[s + 1], e), qf[s + 1][e], s1, 0, 0, 0);
+      }
+    float sc[4], mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int key = kb + 4 * g + i;
+      sc[i] = key > qpos || key >= kv_end ? -INFINITY : s0[i] + s1[i];
+      mx = fmaxf(mx, sc[i]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     const float m_new = fmaxf(m, mx);
-    const float alpha = (m_new == -INFINITY) ? 1.f : __expf(m - m_new);
+    const float alpha = m_new == -INFINITY ? 1.f : __expf(m - m_new);
     float ps = 0.f;
 #pragma unroll
-    for (int jj = 0; jj < KT / 4; ++jj) {
-      const float pv = (sc[jj] == -INFINITY) ? 0.f : __expf(sc[jj] - m_new);
-      Ps[qi][sub + 4 * jj] = pv;
-      ps += pv;
+    for (int i = 0; i < 4; ++i) {
+      sc[i] = sc[i] == -INFINITY ? 0.f : __expf(sc[i] - m_new);
+      ps += sc[i];
     }
-    ps += __shfl_xor(ps, 1, 64);
-    ps += __shfl_xor(ps, 2, 64);
+    ps += __shfl_xor(ps, 16, 64);
+    ps += __shfl_xor(ps, 32, 64);
     l = l * alpha + ps;
     m = m_new;
 #pragma unroll
-    for (int i = 0; i < DPT; ++i) acc[i] *= alpha;
-    __syncthreads();
-    for (int kk = 0; kk < KT; ++kk) {
-      const float pk = Ps[qi][kk];
+    for (int j = 0; j < NS; ++j) acc[j] *= alpha;
 #pragma unroll
-      for (int i = 0; i < DPT; ++i) acc[i] = fmaf(pk, Vs[kk][sub * DPT + i], acc[i]);
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int x = 0; x < NH; ++x)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+          acc[4 * x + nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(el(vx[i][x], nb), sc[i], acc[4 * x + nb], 0, 0, 0);
+    if (more) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) kx[s] = kn[s];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int x = 0; x < NH; ++x) vx[i][x] = vn[i][x];
     }
   }
-  if (valid) {
-    const float inv = 1.0f / l;
-    T* dst = o + (size_t)(t0 + q_lo + qi) * d + h * DH + sub * DPT;
+  if (g == 0) {
+    wm[wave][r] = m;
+    wl[wave][r] = l;
+  }
 #pragma unroll
-    for (int i = 0; i < DPT; ++i) st<T>(dst, i, acc[i] * inv);
+  for (int x = 0; x < NH; ++x)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *(float4*)&wo[wave][r][64 * x + 16 * g + 4 * i] =
+          float4{acc[4 * x][i], acc[4 * x + 1][i], acc[4 * x + 2][i], acc[4 * x + 3][i]};
+  __syncthreads();
+  for (int idx = tid; idx < 16 * DH; idx += 256) {
+    const int q = idx / DH, dd = idx % DH;
+    if (q_lo + q >= n) break;
+    float M = wm[0][q];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) M = fmaxf(M, wm[w][q]);
+    float L = 0.f, A = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      if (wm[w][q] == -INFINITY) continue;  // a wave without keys for this query
+      const float f = __expf(wm[w][q] - M);
+      L += wl[w][q] * f;
+      A += wo[w][q][dd] * f;
+    }
+    o[(size_t)(t0 + q_lo + q) * d + h * DH + dd] = A / L;
   }
 }
 
@@ -764,25 +833,20 @@ template <int DH> constexpr size_t ext_lds() {
   return tiles > merge ? tiles : merge;
 }
 
-template <typename T>
-static hipError_t prefill_t(const float* qkv, Segs sg, int H, int dh, KvPages kp, const float2* rope, const void* k,
-                            const void* v, void* o, hipStream_t s) {
-  const dim3 grid((sg.max_len + 63) / 64, H, sg.n_seg);
-  const float scale = 1.0f / sqrtf((float)dh);
-  if (dh == 64)
-    hipLaunchKernelGGL((k_attn_prefill<T, 64>), grid, dim3(256), 0, s, qkv, sg.row, sg.pos, sg.off, H, kp, rope,
-                       (const T*)k, (const T*)v, (T*)o, scale);
-  else
-    hipLaunchKernelGGL((k_attn_prefill<T, 128>), grid, dim3(256), 0, s, qkv, sg.row, sg.pos, sg.off, H, kp, rope,
-                       (const T*)k, (const T*)v, (T*)o, scale);
-  return hipGetLastError();
-}
-
 hipError_t attn_prefill(int ct, const float* qkv, Segs sg, int H, int dh, KvPages kp, const float2* rope,
                         const void* kslab, const void* vslab, void* o, hipStream_t s) {
   if (sg.n_tok <= 0) return hipSuccess;
-  if (ct == DT_F32) return prefill_t<float>(qkv, sg, H, dh, kp, rope, kslab, vslab, o, s);
   const float scale = 1.0f / sqrtf((float)dh);
+  if (ct == DT_F32) {
+    const dim3 grid((sg.max_len + 15) / 16, H, sg.n_seg);
+    if (dh == 64)
+      hipLaunchKernelGGL((k_attn_f32<64>), grid, dim3(256), 0, s, qkv, sg.row, sg.pos, sg.off, H, kp, rope,
+                         (const float*)kslab, (const float*)vslab, (float*)o, scale, sg.order);
+    else
+      hipLaunchKernelGGL((k_attn_f32<128>), grid, dim3(256), 0, s, qkv, sg.row, sg.pos, sg.off, H, kp, rope,
+                         (const float*)kslab, (const float*)vslab, (float*)o, scale, sg.order);
+    return hipGetLastError();
+  }
   if (sg.max_len <= 16) {  // short segments: keys split over the waves
     const dim3 grid(1, H, sg.n_seg);
     if (dh == 64)

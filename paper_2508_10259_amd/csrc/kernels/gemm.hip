@@ -14,7 +14,7 @@
 //    128x128x64 tiles, 4 waves each owning 64x64 as 4x4 MFMA 16x16x32 blocks,
 //    LDS double buffering with one barrier per K step, epilogue staged
 //    through LDS so global stores are row-contiguous.
-//  * k_gemm_f32     (fp32 model dtype): 64x64x16 FMA tiles, same epilogue.
+//  fp32 models: gemm_f32.hip, same epilogues.
 #include <type_traits>
 
 #include "common.h"
@@ -662,51 +662,6 @@ static bool big_narrow(int M, int N) {
 }
 
 // ----------------------------------------------------------------------------
-// fp32 model dtype
-
-constexpr int FBM = 64, FBN = 64, FBK = 16;
-
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ u, const float* __restrict__ W,
-                                                  int M, int K, void* __restrict__ out, int ldo) {
-  constexpr int LDC = FBN + 4;
-  __shared__ float As[FBK][FBM + 4], Bs[FBK][FBN + 4];
-  __shared__ float Cs[FBM * LDC];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * FBM, n0 = blockIdx.x * FBN;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += FBK) {
-    for (int idx = tid; idx < FBM * FBK; idx += 256) {
-      const int rr = idx / FBK, kk = idx % FBK;
-      As[kk][rr] = (m0 + rr < M) ? u[(size_t)(m0 + rr) * K + k0 + kk] : 0.f;
-      Bs[kk][rr] = W[(size_t)(n0 + rr) * K + k0 + kk];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < FBK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) Cs[(ty * 4 + i) * LDC + tx * 4 + j] = acc[i][j];
-  __syncthreads();
-  tile_epilogue<EPI, float, FBM, FBN>(Cs, m0, n0, M, out, ldo);
-}
-
-// ----------------------------------------------------------------------------
-
-// ----------------------------------------------------------------------------
 // wide decode GEMM: 16 < M <= 64 tokens (batched decode), split-K partial sums
 //
 // A workgroup owns 128 weight rows (8 waves x 16) and one K split.  Every
@@ -1245,11 +1200,7 @@ static hipError_t gemm_epi(int ct, const void* u, const void* W, int M, int N, i
     if (olo && EPI == EPI_STORE) return hipErrorInvalidValue;
     if (olo && EPI == EPI_RESID && !o16) return hipErrorInvalidValue;
   }
-  if (ct == DT_F32) {
-    hipLaunchKernelGGL((k_gemm_f32<EPI>), dim3(N / FBN, (M + FBM - 1) / FBM), dim3(256), 0, s,
-                       (const float*)u, (const float*)W, M, K, out, ldo);
-    return hipGetLastError();
-  }
+  if (ct == DT_F32) return gemm_f32(EPI, (const float*)u, (const float*)W, M, N, K, (float*)out, ldo, s);
   if (M <= 64) {
     const SkinnyArgs a{(const f16*)u, (const f16*)ulo, 0.f, (const f16*)W, M, K, out, ldo, (f16*)o16, (f16*)olo};
     return skinny_dispatch<EPI, false>(a, N, s);

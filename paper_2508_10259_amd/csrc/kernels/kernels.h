@@ -59,6 +59,15 @@ constexpr int GU_BLOCK = 16;
 hipError_t gemm(int ct, int epi, const void* u, const void* W, int M, int N, int K, void* out,
                 int ldo, hipStream_t s, const void* ulo = nullptr, void* o16 = nullptr, void* olo = nullptr);
 
+// The fp32 forms (gemm() takes gemm_f32 for fp32 models).  gemv_f32: M <= 64, K a
+// multiple of 64; norm (STORE, SWIGLU): x is the residual stream and the result is
+// divided by the rms of its rows, sqrt(mean(x^2) + eps); splits > 1 (RESID): the
+// K range in `splits` parts, part holding splits * M * N floats and cnt N / 16
+// counters, zero before the first call and left zero.
+hipError_t gemm_f32(int epi, const float* u, const float* W, int M, int N, int K, float* out, int ldo, hipStream_t s);
+hipError_t gemv_f32(int epi, const float* x, bool norm, float eps, const float* W, int M, int N, int K, float* out,
+                    int ldo, hipStream_t s, int splits = 1, float* part = nullptr, unsigned* cnt = nullptr);
+
 // Split-K decode GEMV (fp16, M <= 64): part[s][m][n] = sum over the s-th of
 // `splits` equal K ranges (in 128-wide chunks) of u[m][k] W[n][k], with u the
 // fp16 input or the pair u + ulo as in gemm().  part holds splits * M * N floats.

@@ -13,6 +13,11 @@ int ams_probe_gemm(int dtype, int epi, const void* u, const void* ulo, const voi
   return (int)ams::gemm(dtype, epi, u, W, M, N, K, out, ldo, (hipStream_t)stream, ulo, o16, olo);
 }
 
+int ams_probe_gemv_f32(int epi, const float* x, int norm, float eps, const float* W, int M, int N, int K, float* out,
+                       int ldo, int splits, float* part, unsigned* cnt, void* stream) {
+  return (int)ams::gemv_f32(epi, x, norm != 0, eps, W, M, N, K, out, ldo, (hipStream_t)stream, splits, part, cnt);
+}
+
 int ams_probe_gemm_big(int epi, const void* u, const void* W, int M, int N, int K, void* out, int ldo, int bn,
                        void* stream) {
   return (int)ams::gemm_big(epi, u, W, M, N, K, out, ldo, (hipStream_t)stream, bn);
