@@ -27,7 +27,10 @@ static bool fused_norm(const Ctx& c, int rows) { return c.model->ct == DT_F16 &&
 // fp32 passes of up to 64 tokens run gemv_f32, which applies the RMSNorm itself.
 static bool short_f32(const Model& md, int M) { return md.ct == DT_F32 && M <= 64; }
 
-// h += x W^T of such a pass, K split over more workgroups for long rows.
+// fp16 token passes longer than that run gemm_tokens on the fragment-ordered weights.
+static bool tiled_f16(const Model& md, int M) { return md.ct == DT_F16 && M > 64; }
+
+// h += x W^T of a short fp32 pass, K split over more workgroups for long rows.
 static hipError_t resid_f32(const Ctx& c, const void* x, const void* W, int M, int K, float* h, hipStream_t s) {
   const int d = c.model->cfg.d_model;
   return gemv_f32(EPI_RESID, (const float*)x, false, 0.f, (const float*)W, M, d, K, h, d, s, f32_split(d, K), c.kpart(),
@@ -295,20 +298,22 @@ static bool kv_fusable(const Ctx& c, int M) {
   return c.model->ct == DT_F16 && gemm_qkv_fusable(M, 3 * m.d_model, m.head_dim, m.d_model);
 }
 
-// h += x W^T over the M tokens of a token pass (K inputs per token).  At
-// medium token counts in fp16 the 256 x 256-tile GEMM splits K and a reduction
-// adds the partial sums in split order; that reduction also leaves the next
+// h += x W^T over the M tokens of a token pass (K inputs per token; Wf: W in
+// fragment order, fp16 models).  Where its tiles alone would leave CUs idle the
+// fp16 GEMM splits K and a reduction adds the partial sums in split order; that reduction also leaves the next
 // RMSNorm's output in u (normed = true), which saves the norm its own pass
 // over h (7B, 1,024-token extension: 6.4 us per norm).
-static hipError_t tokens_resid(Ctx& c, const void* x, const void* W, int M, int K, hipStream_t s, bool& normed) {
+static hipError_t tokens_resid(Ctx& c, const void* x, const void* W, const void* Wf, int M, int K, hipStream_t s,
+                               bool& normed) {
   const Model& md = *c.model;
   const int d = md.cfg.d_model;
-  const int splits = md.ct == DT_F16 ? prefill_ksplit(M, d, K) : 1;
   normed = false;
   if (short_f32(md, M)) return resid_f32(c, x, W, M, K, c.h(), s);
-  if (splits > 1) {
-    hipError_t e = gemm_big_part(x, W, M, d, K, splits, c.kpart(), s);
-    if (e == hipSuccess) e = resid_norm(c.kpart(), splits, M, d, c.h(), md.cfg.rms_eps, c.u(), s);
+  if (tiled_f16(md, M)) {
+    const TokPlan p = tok_plan(M, d, K, true);
+    if (p.splits == 1) return gemm_tokens_tile(p.tile, EPI_RESID, x, Wf, M, d, K, c.h(), d, 1, s);
+    hipError_t e = gemm_tokens_tile(p.tile, EPI_PART, x, Wf, M, d, K, c.kpart(), d, p.splits, s);
+    if (e == hipSuccess) e = resid_norm(c.kpart(), p.splits, M, d, c.h(), md.cfg.rms_eps, c.u(), s);
     normed = e == hipSuccess;
     return e;
   }
@@ -326,14 +331,17 @@ static hipError_t layer_tokens(Ctx& c, int l, int M, const Segs& sg, hipStream_t
   const Cfg& m = md.cfg;
   const int d = m.d_model, F = m.d_ffn, dt = md.ct;
   const bool f32s = short_f32(md, M);  // the projections then normalise h themselves
+  const bool tiled = tiled_f16(md, M);
   if (!u_ready && !f32s) TRY(rmsnorm(dt, c.h(), M, d, m.rms_eps, c.u(), s));
   if (kv_fused) {  // the QKV GEMM's epilogue appends K/V (the token tables are the pass's)
     KvEpi kv{(const int64_t*)(c.ws + c.lay.tok_base), (const int32_t*)(c.ws + c.lay.tok_pos), c.kslab(l), c.vslab(l),
              c.rope(), d, m.head_dim};
-    TRY(gemm_qkv_kv(c.u(), md.wqkv(l), M, d, c.qkv(), kv, s));
+    TRY(gemm_qkv_kv(c.u(), md.fqkv(l), M, d, c.qkv(), kv, s));
   } else {
     if (f32s)
       TRY(gemv_f32(EPI_STORE, c.h(), true, m.rms_eps, (const float*)md.wqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
+    else if (tiled)
+      TRY(gemm_tokens(EPI_STORE, c.u(), md.fqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
     else
       TRY(gemm(dt, EPI_STORE, c.u(), md.wqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
     if (tables)  // each token's slot from the pass's tables (7B batch-64 extension: 19.05 -> 18.92 ms per step)
@@ -344,13 +352,15 @@ static hipError_t layer_tokens(Ctx& c, int l, int M, const Segs& sg, hipStream_t
   }
   TRY(attn_prefill(dt, c.qkv(), sg, m.n_heads, m.head_dim, c.pages(), c.rope(), c.kslab(l), c.vslab(l), c.o(),
                    s));
-  TRY(tokens_resid(c, c.o(), md.wo(l), M, d, s, u_ready));
+  TRY(tokens_resid(c, c.o(), md.wo(l), md.fo(l), M, d, s, u_ready));
   if (!u_ready && !f32s) TRY(rmsnorm(dt, c.h(), M, d, m.rms_eps, c.u(), s));
   if (f32s)
     TRY(gemv_f32(EPI_SWIGLU, c.h(), true, m.rms_eps, (const float*)md.wgu(l), M, 2 * F, d, (float*)c.a(), F, s));
+  else if (tiled)
+    TRY(gemm_tokens(EPI_SWIGLU, c.u(), md.fgu(l), M, 2 * F, d, c.a(), F, s));
   else
     TRY(gemm(dt, EPI_SWIGLU, c.u(), md.wgu(l), M, 2 * F, d, c.a(), F, s));
-  TRY(tokens_resid(c, c.a(), md.wd(l), M, F, s, u_ready));
+  TRY(tokens_resid(c, c.a(), md.wd(l), md.fd(l), M, F, s, u_ready));
   return hipSuccess;
 }
 

@@ -15,6 +15,8 @@
 #include <unordered_map>
 #include <vector>
 
+#include "gemm_plan.h"
+
 #include "fused_limits.h"
 
 namespace ams {
@@ -196,33 +198,6 @@ inline int fused_split_attn(const Cfg& c, int rows, int capacity, int grid) {
   return s;
 }
 
-// K splits of a residual projection of a token pass (fp16; N = d_model output
-// rows, K inputs): the 256 x 256-tile GEMM takes token counts whose tiles number
-// 160 or more unsplit; below that, when N is a multiple of 256 and the pass has
-// more than 64 tokens, its K steps (of 64) are cut so that tiles x splits
-// reaches about 256 workgroups, each keeping at least 8 K steps.
-inline int prefill_ksplit(int M, int N, int K) {
-  if (M <= 64 || N % 256 != 0 || K % 64 != 0) return 1;
-  const int tiles = (N / 256) * ((M + 255) / 256);
-  if (tiles >= 160) return 1;
-  return std::max(1, std::min((256 + tiles - 1) / tiles, (K / 64) / 8));
-}
-
-// Floats of split-K partial sums the token passes of a context need (at most
-// pass_tokens tokens per pass; the O projection has K = d, the down projection
-// K = F).
-inline size_t prefill_part_floats(const Cfg& c, int pass_tokens) {
-  size_t best = 0;
-  const int d = c.d_model, F = c.d_ffn;
-  for (int M = 65; M <= pass_tokens; M = M < 256 ? 256 : M + 256) {
-    const int m = std::min(M, pass_tokens);
-    const int s = std::max(prefill_ksplit(m, d, d), prefill_ksplit(m, d, F));
-    if (s > 1) best = std::max(best, (size_t)s * m * d);
-    if ((d / 256) * ((m + 255) / 256) >= 160) break;
-  }
-  return best;
-}
-
 // K splits of an fp32 residual projection of up to 64 tokens (16-row strips,
 // one workgroup each): a strip's weights (64 K bytes) are kept to about 64 KB per
 // split while the splits' strips number at most 256, one per CU.  Merging the
@@ -286,7 +261,8 @@ inline CtxLayout ctx_layout(const Cfg& c, int batch, int capacity, int pass_toke
                    decode_wsplit(2 * (int)F, (int)d) * B * 2 * F, decode_wsplit((int)d, (int)F) * B * d,
                    decode_wsplit((int)NB, (int)d) * B * NB});
   }
-  if (es == 2) kp = std::max(kp, prefill_part_floats(c, (int)x.pass_tokens));
+  if (es == 2)
+    kp = std::max({kp, tok_part_floats((int)d, (int)d, x.pass_tokens), tok_part_floats((int)d, (int)F, x.pass_tokens)});
   else kp = std::max(kp, (size_t)std::max(f32_split((int)d, (int)d), f32_split((int)d, (int)F)) * std::min<size_t>(T, 64) * d);
   x.kpart = o; o = align256(o + kp * 4);
   x.part = o; o = align256(o + B * (size_t)c.n_heads * x.max_splits * (c.head_dim + 2) * 4);

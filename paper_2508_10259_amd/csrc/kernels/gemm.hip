@@ -10,13 +10,9 @@
 //    SiLU-gate) runs on the reduced values.  Up to 16 tokens it can also
 //    apply the preceding RMSNorm itself (gemv_rmsnorm).  RMSNorm gains are
 //    folded into the packed weights, so every GEMM consumes h / rms(h).
-//  * k_gemm_tiled   (fp16, M > 64: prefix build and observation extension).
-//    128x128x64 tiles, 4 waves each owning 64x64 as 4x4 MFMA 16x16x32 blocks,
-//    LDS double buffering with one barrier per K step, epilogue staged
-//    through LDS so global stores are row-contiguous.
+//  * k_gemm_wide    (fp16, batched decode of 9 to 64 rows).
+//  Longer token passes: gemm_tokens.hip.
 //  fp32 models: gemm_f32.hip, same epilogues.
-#include <type_traits>
-
 #include "common.h"
 #include "kernels.h"
 
@@ -285,380 +281,6 @@ static hipError_t skinny_dispatch(const SkinnyArgs& a, int N, hipStream_t s) {
     }
   }
   return hipErrorInvalidValue;
-}
-
-// ----------------------------------------------------------------------------
-// shared epilogue for tiles staged in LDS as Cs[BM][BN + 4] (fp32)
-
-template <int EPI, typename TO, int BM, int BN>
-__device__ __forceinline__ void tile_epilogue(const float* Cs, int m0, int n0, int M, void* out, int ldo) {
-  constexpr int LDC = BN + 4;
-  if constexpr (EPI == EPI_SWIGLU) {
-    constexpr int OC = BN / 2;
-    for (int idx = threadIdx.x; idx < BM * OC; idx += blockDim.x) {
-      const int rr = idx / OC, c = idx % OC;
-      if (m0 + rr >= M) continue;
-      const int blk = c / GU_BLOCK, j = c % GU_BLOCK;
-      const float gt = Cs[rr * LDC + blk * 2 * GU_BLOCK + j];
-      const float up = Cs[rr * LDC + blk * 2 * GU_BLOCK + GU_BLOCK + j];
-      st<TO>((TO*)out, (size_t)(m0 + rr) * ldo + (n0 >> 1) + c, silu(gt) * up);
-    }
-  } else {
-    for (int idx = threadIdx.x; idx < BM * BN; idx += blockDim.x) {
-      const int rr = idx / BN, c = idx % BN;
-      if (m0 + rr >= M) continue;
-      float* p = (float*)out + (size_t)(m0 + rr) * ldo + n0 + c;
-      if constexpr (EPI == EPI_STORE) *p = Cs[rr * LDC + c];
-      else *p += Cs[rr * LDC + c];
-    }
-  }
-}
-
-// ----------------------------------------------------------------------------
-// tiled f16 MFMA: M > 64
-
-// Tile rows of TBK + 16 halves (160 bytes): the fragment reads and the staging
-// writes (8 lanes fill one row) are free of LDS bank conflicts on gfx950.
-constexpr int TBM = 128, TBN = 128, TBK = 64, TLDK = TBK + 16;
-constexpr int T_AB_BYTES = 2 * 2 * TBM * TLDK * 2;  // double-buffered A and B tiles (fp16)
-constexpr int T_C_BYTES = TBM * (TBN + 4) * 4;      // fp32 staging for the epilogue
-constexpr int T_LDS = T_AB_BYTES > T_C_BYTES ? T_AB_BYTES : T_C_BYTES;
-
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_tiled(const f16* __restrict__ u, const f16* __restrict__ W,
-                                                    int M, int K, void* __restrict__ out, int ldo) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[T_LDS];
-  f16* As = (f16*)smem;                  // [2][TBM][TLDK]
-  f16* Bs = As + 2 * TBM * TLDK;          // [2][TBN][TLDK]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 15, g = lane >> 4;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int m0 = blockIdx.y * TBM, n0 = blockIdx.x * TBN;
-
-  // global -> register mapping: thread loads the 16-byte k chunk tid & 7 of rows
-  // tid / 8 + 32 q (q < 4) of A and of B
-  const int lrow = tid >> 3, lk = (tid & 7) * 8;
-  bool aok[4];
-  const f16* ag[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    aok[q] = m0 + lrow + 32 * q < M;
-    ag[q] = u + (size_t)(aok[q] ? m0 + lrow + 32 * q : 0) * K + lk;
-  }
-  const f16* bg = W + (size_t)(n0 + lrow) * K + lk;
-
-  uint4 ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
-#define AMS_GLOAD(k0)                                                                  \
-  do {                                                                                 \
-    const uint4 z = {0u, 0u, 0u, 0u};                                                  \
-    ra0 = aok[0] ? *(const uint4*)(ag[0] + (k0)) : z;                                  \
-    ra1 = aok[1] ? *(const uint4*)(ag[1] + (k0)) : z;                                  \
-    ra2 = aok[2] ? *(const uint4*)(ag[2] + (k0)) : z;                                  \
-    ra3 = aok[3] ? *(const uint4*)(ag[3] + (k0)) : z;                                  \
-    rb0 = *(const uint4*)(bg + (k0));                                                  \
-    rb1 = *(const uint4*)(bg + (size_t)32 * K + (k0));                                 \
-    rb2 = *(const uint4*)(bg + (size_t)64 * K + (k0));                                 \
-    rb3 = *(const uint4*)(bg + (size_t)96 * K + (k0));                                 \
-  } while (0)
-#define AMS_LSTORE(buf)                                                                \
-  do {                                                                                 \
-    f16* a_ = As + ((buf) * TBM + lrow) * TLDK + lk;                                   \
-    f16* b_ = Bs + ((buf) * TBN + lrow) * TLDK + lk;                                   \
-    *(uint4*)a_ = ra0; *(uint4*)(a_ + 32 * TLDK) = ra1;                                \
-    *(uint4*)(a_ + 64 * TLDK) = ra2; *(uint4*)(a_ + 96 * TLDK) = ra3;                  \
-    *(uint4*)b_ = rb0; *(uint4*)(b_ + 32 * TLDK) = rb1;                                \
-    *(uint4*)(b_ + 64 * TLDK) = rb2; *(uint4*)(b_ + 96 * TLDK) = rb3;                  \
-  } while (0)
-
-  f32x4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int KT = K / TBK;
-  AMS_GLOAD(0);
-  AMS_LSTORE(0);
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < KT) AMS_GLOAD((kt + 1) * TBK);
-#pragma unroll
-    for (int ks = 0; ks < TBK / 32; ++ks) {
-      half8 af[4], bfr[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        af[i] = *(const half8*)(As + (cur * TBM + wm * 64 + i * 16 + r) * TLDK + ks * 32 + g * 8);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        bfr[j] = *(const half8*)(Bs + (cur * TBN + wn * 64 + j * 16 + r) * TLDK + ks * 32 + g * 8);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < KT) AMS_LSTORE(cur ^ 1);
-    __syncthreads();
-  }
-#undef AMS_GLOAD
-#undef AMS_LSTORE
-
-  // C block (i, j): lane holds rows 4g..4g+3 (tokens) of column r (weight row)
-  float* Cs = (float*)smem;
-  constexpr int LDC = TBN + 4;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        Cs[(wm * 64 + i * 16 + 4 * g + e) * LDC + wn * 64 + j * 16 + r] = acc[i][j][e];
-  __syncthreads();
-  tile_epilogue<EPI, f16, TBM, TBN>(Cs, m0, n0, M, out, ldo);
-}
-
-// ----------------------------------------------------------------------------
-// big f16 MFMA tiles: large prefix builds (enough 256 x 256 tiles to fill the chip)
-//
-// 256 (tokens) x 256 (weight rows) per workgroup, eight waves of 64 x 128
-// (4 x 2), K steps of 64 double-buffered in LDS.  The tiles move from global
-// memory straight into LDS (global_load_lds_dwordx4: each wave instruction
-// fills 1 KB of LDS, lane i the i-th 16 bytes), so no registers stage them.
-// A tile row is 128 bytes (8 chunks of 16); chunk c of row R sits in slot
-// c ^ (R & 7), which the DMA realises by choosing each lane's source chunk,
-// and which keeps the 16-byte fragment reads of 8 consecutive rows on 8
-// distinct bank groups.  A wave reuses each A fragment for 8 B fragments and
-// each B fragment for 4 A fragments.  The epilogue runs from registers: a lane
-// holds 4 consecutive tokens of one weight row per 16 x 16 block, and the gate
-// and up blocks of a SwiGLU pair sit side by side in the same lane.  With
-// EPI_PART the K steps are cut into gridDim.y splits, each writing its partial
-// sums (for medium token counts, where the tiles alone leave CUs idle).
-
-constexpr int GBM = 256, GBN = 256, GBK = 64;
-constexpr int G_TILE = 256 * 128;         // bytes of one 256-row A or B tile (rows of 64 fp16)
-
-// LDS of a BN-wide tile pair, double-buffered: [2 stages][A tile | B tile]
-template <int BN> constexpr int g_lds() { return 2 * (G_TILE + BN * 128); }
-
-typedef __attribute__((address_space(3))) void* lds_ptr;
-
-// DMA of one K step: wave w moves 1 KB blocks 4w..4w+3 of the A tile and
-// BN/64 blocks of the B tile (8 rows each).  Lane i of a block: row R0 + i/8,
-// slot i%8, source chunk (i%8) ^ (row & 7).  A rows past the last valid one
-// (alast) read it again: they only feed outputs that are never stored.
-template <int BN>
-__device__ __forceinline__ void big_dma(unsigned char* stage, const f16* A, const f16* B, int K, int k0, int alast,
-                                        int wave, int lane) {
-  constexpr int BQ = BN / 64;  // B blocks per wave
-  const int slot = lane & 7;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int blk = wave * 4 + q;
-    const int row = blk * 8 + (lane >> 3);
-    const int c = slot ^ (row & 7);
-    const int ar = row <= alast ? row : alast;
-    __builtin_amdgcn_global_load_lds((const void*)(A + (size_t)ar * K + k0 + c * 8), (lds_ptr)(stage + blk * 1024),
-                                     16, 0, 0);
-    if (q < BQ) {
-      const int bblk = wave * BQ + q;
-      const int brow = bblk * 8 + (lane >> 3);
-      const int bc = slot ^ (brow & 7);
-      __builtin_amdgcn_global_load_lds((const void*)(B + (size_t)brow * K + k0 + bc * 8),
-                                       (lds_ptr)(stage + G_TILE + bblk * 1024), 16, 0, 0);
-    }
-  }
-}
-
-// BN = 256, or 192 / 128 for shapes whose 256-wide tiles leave a round of CUs
-// mostly idle (QKV of the 1,024-token extension: 192 tiles of 256 x 256 on 256
-// CUs, 256 tiles of 256 x 192; the columns past whole rounds of gate|up there
-// as 256 x 128 tiles); each wave then covers 64 x BN/2.
-template <int EPI, int BN = GBN>
-__global__ __launch_bounds__(512) void k_gemm_big(const f16* __restrict__ u, const f16* __restrict__ W, int M,
-                                                  int N, int K, void* __restrict__ out, int ldo, KvEpi kv) {
-  constexpr int WN = BN / 2, NJ = WN / 16;  // weight rows per wave, 16-row blocks per wave
-  constexpr int STAGE = G_TILE + BN * 128;
-  static_assert(EPI != EPI_SWIGLU || NJ % 2 == 0, "gate and up blocks come in pairs");
-  extern __shared__ __attribute__((aligned(16))) unsigned char gsm[];  // [2 stages][A tile | B tile]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 15, g = lane >> 4;
-  const int wm = wave >> 1, wn = wave & 1;  // wave tile: tokens wm*64.., weight rows wn*WN..
-  // tile order: workgroups are dispatched round-robin over the 8 XCDs, so XCD x
-  // (ids = x mod 8) takes a contiguous range of the tile sequence, which walks
-  // groups of 8 token tiles down each weight tile: tiles that share a weight
-  // (or token) tile run close together on one XCD's L2
-  const int tm_n = (M + GBM - 1) / GBM, tn_n = N / BN, T = tm_n * tn_n;
-  const int L = blockIdx.x, xcd = L & 7, per = T >> 3, rem = T & 7;
-  const int Lx = xcd * per + (xcd < rem ? xcd : rem) + (L >> 3);
-  const int grp = Lx / (8 * tn_n), first_m = grp * 8;
-  const int gm = tm_n - first_m < 8 ? tm_n - first_m : 8;
-  const int in_grp = Lx - grp * 8 * tn_n;
-  const int m0 = (first_m + in_grp % gm) * GBM, n0 = (in_grp / gm) * BN;
-  const int alast = M - 1 - m0;  // last valid A row of this tile (>= 0)
-  // K steps of this workgroup: split blockIdx.y of gridDim.y (EPI_PART; one split otherwise)
-  const int KT_all = K / GBK, sp = blockIdx.y, S = gridDim.y;
-  const int kt0 = sp * KT_all / S, kt1 = (sp + 1) * KT_all / S;
-  const f16* A = u + (size_t)m0 * K + (size_t)kt0 * GBK;
-  const f16* B = W + (size_t)n0 * K + (size_t)kt0 * GBK;
-
-  f32x4 acc[4][NJ];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // fragment rows of this lane: A rows wm*64 + 16 i + r, B rows wn*WN + 16 j + r (all = r mod 8)
-  const int sw = r & 7;
-  const int KT = kt1 - kt0;
-  big_dma<BN>(gsm, A, B, K, 0, alast, wave, lane);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    unsigned char* cur = gsm + (kt & 1) * STAGE;
-    if (kt + 1 < KT) big_dma<BN>(gsm + ((kt + 1) & 1) * STAGE, A, B, K, (kt + 1) * GBK, alast, wave, lane);
-    const unsigned char* Ab = cur + (wm * 64 + r) * 128;
-    const unsigned char* Bb = cur + G_TILE + (wn * WN + r) * 128;
-    // every fragment of the K step requested in use order, the MFMA groups (8
-    // MFMAs: two B fragments times four A fragments) interleaved with the
-    // requests of the fragments two groups ahead, so a group does not wait on
-    // the LDS round trip of its own operands (on the 7B builds 1.5-2.5% faster
-    // than the compiler's order, which requested each group's fragments right
-    // before it)
-    half8 af[2][4], bfr[2][NJ];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int off = (((4 * ks + g) ^ sw) << 4);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) af[ks][i] = *(const half8*)(Ab + i * 16 * 128 + off);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) bfr[ks][j] = *(const half8*)(Bb + j * 16 * 128 + off);
-    }
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[ks][i], bfr[ks][j], acc[i][j], 0, 0, 0);
-    if constexpr (NJ == 8) {  // sched_group_barrier masks: 0x100 LDS reads, 0x008 MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-    }
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's DMA into the other stage has landed
-    __syncthreads();
-  }
-
-  // block (i, j): lane holds tokens tm + 4g + e of weight row tn + r
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int tm = m0 + wm * 64 + i * 16 + 4 * g;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int tok = tm + e;
-      if (tok >= M) continue;
-      if constexpr (EPI == EPI_SWIGLU) {
-        // blocks 2p (gate) and 2p+1 (up) of the packed interleave; output column (n >> 1) + r
-#pragma unroll
-        for (int pr = 0; pr < NJ / 2; ++pr) {
-          const int col = ((n0 + wn * WN) >> 1) + pr * 16 + r;
-          st<f16>((f16*)out, (size_t)tok * ldo + col, silu(acc[i][2 * pr][e]) * acc[i][2 * pr + 1][e]);
-        }
-      } else if (EPI == EPI_QKV && n0 + wn * WN >= kv.d) {
-        // k or v columns (a wave's 128 columns lie in one of q, k, v: d is a multiple of
-        // 256): heads c / dh .. of this wave, written to the token's pool slot as
-        // k_kv_append writes them (k rotated by the token's position, rotate-half)
-        const int c0 = n0 + wn * WN;
-        const bool isk = c0 < 2 * kv.d;
-        const size_t base = (size_t)kv.tok_base[tok];
-        const int hd0 = (c0 - (isk ? kv.d : 2 * kv.d)) / kv.dh;
-        // rotate-half pairs: dims dd and dd + dh/2 of a head are blocks jj and jj + HB/2
-        // of its HB = dh/16 blocks (the block index a constant: acc stays in registers)
-        auto kstore = [&](auto hbc) __attribute__((always_inline)) {
-          constexpr int HB = decltype(hbc)::value;
-          const int p = kv.tok_pos[tok], half = HB * 8;
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            const int hh = j / HB, jj = j % HB;  // head of this wave, block within the head
-            if (jj < HB / 2) {
-              const int dd = 16 * jj + r;  // < half; its partner is dd + half
-              const float2 cs = kv.rope[(size_t)p * half + dd];
-              const float a = acc[i][j][e], c = acc[i][(j + HB / 2) % NJ][e];
-              f16* dst = (f16*)kv.k + base + (size_t)(hd0 + hh) * KV_PAGE * (2 * half);
-              st<f16>(dst, dd, a * cs.x - c * cs.y);
-              st<f16>(dst, dd + half, a * cs.y + c * cs.x);
-            }
-          }
-        };
-        if (isk) {
-          if (kv.dh == 128) kstore(std::integral_constant<int, 8>{});
-          else kstore(std::integral_constant<int, 4>{});
-        } else {
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            const int col = 16 * j + r, hh = col / kv.dh, dd = col % kv.dh;
-            st<f16>((f16*)kv.v + base + (size_t)(hd0 + hh) * KV_PAGE * kv.dh, dd, acc[i][j][e]);
-          }
-        }
-      } else {
-        // EPI_PART: this split's partial sums at out[sp][tok][n] (ldo = N)
-        const size_t rowo = ((size_t)(EPI == EPI_PART ? sp * M : 0) + tok) * ldo;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          float* p = (float*)out + rowo + n0 + wn * WN + j * 16 + r;
-          if constexpr (EPI == EPI_RESID) *p += acc[i][j][e];
-          else *p = acc[i][j][e];
-        }
-      }
-    }
-  }
-}
-
-template <int EPI, int BN = GBN>
-static hipError_t launch_big(const f16* u, const f16* W, int M, int N, int K, void* out, int ldo, hipStream_t s,
-                             int splits = 1, const KvEpi& kv = KvEpi{}) {
-  hipLaunchKernelGGL((k_gemm_big<EPI, BN>), dim3((N / BN) * ((M + GBM - 1) / GBM), splits), dim3(512), g_lds<BN>(),
-                     s, u, W, M, N, K, out, ldo, kv);
-  return hipGetLastError();
-}
-
-// 256 x 256 tile columns that fill whole rounds of the CUs, when the rest
-// would leave a last round less than half busy and a round is whole tile
-// columns (256 / token tiles an integer); gemm() runs the remaining weight rows
-// as 256 x 128 tiles.  At 1,024 tokens the 7B gate|up projection's 344 big
-// tiles become 256 (64 columns) + 176 half-width ones for 88 big ones' work.
-static int big_main_cols(int M, int N) {
-  const int tm = (M + GBM - 1) / GBM, tn = N / GBN;
-  if (256 % tm != 0) return tn;
-  const int per_round = 256 / tm;
-  const int full = tn / per_round * per_round, rest = tn - full;
-  if (full == 0 || rest == 0 || 2 * rest * tm > 256) return tn;
-  return full;
-}
-
-// 256 x 192 tiles when N allows them and they need fewer CU-rounds weighted by
-// tile width (rounds of 256 workgroups, one per CU): ceil(T192 / 256) * 192 <
-// ceil(T256 / 256) * 256.  At 1,024 tokens the 7B QKV projection takes one
-// round of 256 narrower tiles instead of 192 wide ones with 64 CUs idle.
-static bool big_narrow(int M, int N) {
-  if (N % 192 != 0) return false;
-  const long tm = (M + GBM - 1) / GBM;
-  const long r256 = (tm * (N / 256) + 255) / 256, r192 = (tm * (N / 192) + 255) / 256;
-  return r192 * 192 < r256 * 256;
 }
 
 // ----------------------------------------------------------------------------
@@ -1205,66 +827,7 @@ static hipError_t gemm_epi(int ct, const void* u, const void* W, int M, int N, i
     const SkinnyArgs a{(const f16*)u, (const f16*)ulo, 0.f, (const f16*)W, M, K, out, ldo, (f16*)o16, (f16*)olo};
     return skinny_dispatch<EPI, false>(a, N, s);
   }
-  // 256 x 256 tiles from 160 of them on (five in eight CUs busy), 128 x 128 below: on the 7B
-  // shapes the big tiles won at 172 (gate|up, 288 tokens) and 192 (QKV, 1024 tokens) tiles and
-  // lost at 96 and 64
-  if (N % GBN == 0 && (size_t)(N / GBN) * ((M + GBM - 1) / GBM) >= 160) {
-    if constexpr (EPI == EPI_STORE)
-      if (big_narrow(M, N)) return launch_big<EPI, 192>((const f16*)u, (const f16*)W, M, N, K, out, ldo, s);
-    const int nb = big_main_cols(M, N) * GBN;
-    hipError_t e = launch_big<EPI>((const f16*)u, (const f16*)W, M, nb, K, out, ldo, s);
-    if (e != hipSuccess || nb == N) return e;
-    // the weight rows past nb in 256 x 128 tiles (output columns nb / 2 on for SwiGLU):
-    // the 7B gate|up remainder at 1,024 tokens took 81.9 us as 128 x 128 tiles
-    void* o2 = EPI == EPI_SWIGLU ? (void*)((f16*)out + nb / 2) : (void*)((float*)out + nb);
-    return launch_big<EPI, 128>((const f16*)u, (const f16*)W + (size_t)nb * K, M, N - nb, K, o2, ldo, s);
-  }
-  hipLaunchKernelGGL((k_gemm_tiled<EPI>), dim3(N / TBN, (M + TBM - 1) / TBM), dim3(256), 0, s,
-                     (const f16*)u, (const f16*)W, M, K, out, ldo);
-  return hipGetLastError();
-}
-
-bool gemm_qkv_fusable(int M, int N, int dh, int d) {
-  if (M <= 64 || (dh != 64 && dh != 128) || d % 256 != 0 || N != 3 * d) return false;
-  if ((size_t)(N / GBN) * ((M + GBM - 1) / GBM) < 160) return false;  // gemm() takes the tiled kernel
-  return !big_narrow(M, N) && big_main_cols(M, N) == N / GBN;       // ... or other tile widths
-}
-
-hipError_t gemm_qkv_kv(const void* u, const void* W, int M, int K, float* qkv, const KvEpi& kv, hipStream_t s) {
-  if (M <= 0) return hipSuccess;
-  if ((kv.dh != 64 && kv.dh != 128) || kv.d <= 0 || kv.d % 256 != 0 || K % GBK != 0 || !kv.tok_base || !kv.tok_pos ||
-      !kv.k || !kv.v || !kv.rope)
-    return hipErrorInvalidValue;
-  return launch_big<EPI_QKV>((const f16*)u, (const f16*)W, M, 3 * kv.d, K, qkv, 3 * kv.d, s, 1, kv);
-}
-
-hipError_t gemm_big_part(const void* u, const void* W, int M, int N, int K, int splits, float* part, hipStream_t s) {
-  if (M <= 0) return hipSuccess;
-  if (N % GBN != 0 || K % GBK != 0 || splits < 1 || splits > K / GBK) return hipErrorInvalidValue;
-  return launch_big<EPI_PART>((const f16*)u, (const f16*)W, M, N, K, part, N, s, splits);
-}
-
-hipError_t gemm_big(int epi, const void* u, const void* W, int M, int N, int K, void* out, int ldo, hipStream_t s,
-                    int bn) {
-  if (M <= 0) return hipSuccess;
-  if (bn == 192) {
-    if (epi != EPI_STORE || N % 192 != 0 || K % GBK != 0) return hipErrorInvalidValue;
-    return launch_big<EPI_STORE, 192>((const f16*)u, (const f16*)W, M, N, K, out, ldo, s);
-  }
-  if (bn == 128) {
-    if (N % 128 != 0 || K % GBK != 0) return hipErrorInvalidValue;
-    switch (epi) {
-      case EPI_STORE: return launch_big<EPI_STORE, 128>((const f16*)u, (const f16*)W, M, N, K, out, ldo, s);
-      case EPI_RESID: return launch_big<EPI_RESID, 128>((const f16*)u, (const f16*)W, M, N, K, out, ldo, s);
-      default: return launch_big<EPI_SWIGLU, 128>((const f16*)u, (const f16*)W, M, N, K, out, ldo, s);
-    }
-  }
-  if (bn != GBN || N % GBN != 0 || K % GBK != 0) return hipErrorInvalidValue;
-  switch (epi) {
-    case EPI_STORE: return launch_big<EPI_STORE>((const f16*)u, (const f16*)W, M, N, K, out, ldo, s);
-    case EPI_RESID: return launch_big<EPI_RESID>((const f16*)u, (const f16*)W, M, N, K, out, ldo, s);
-    default: return launch_big<EPI_SWIGLU>((const f16*)u, (const f16*)W, M, N, K, out, ldo, s);
-  }
+  return hipErrorInvalidValue;  // longer token passes: gemm_tokens
 }
 
 hipError_t gemm(int ct, int epi, const void* u, const void* W, int M, int N, int K, void* out, int ldo,

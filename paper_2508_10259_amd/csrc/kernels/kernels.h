@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "fused_limits.h"
+#include "gemm_plan.h"
 
 namespace ams {
 
@@ -122,16 +123,15 @@ hipError_t part_swiglu(const float* part, int splits, int M, int N, void* out, v
 hipError_t part_resid(const float* part, int splits, int M, int N, float* h, void* o16, void* olo, hipStream_t s,
                       float* ss = nullptr);
 
-// The 256 x 256-tile fp16 GEMM that gemm() picks for large prefix builds,
-// callable for any M (N a multiple of 256, K of 64); same epilogues.
-// bn: tile width, 256, 128 (N a multiple of 128) or (EPI_STORE, N a multiple of
-// 192) 192; gemm() picks it.
-hipError_t gemm_big(int epi, const void* u, const void* W, int M, int N, int K, void* out, int ldo, hipStream_t s,
-                    int bn = 256);
-// Split-K form of it (1 <= splits <= K/64): part[s][m][n] = the s-th of `splits`
-// equal ranges of K steps of sum_k u[m][k] W[n][k]; part holds splits * M * N
-// floats.  part_resid adds them to the residual.
-hipError_t gemm_big_part(const void* u, const void* W, int M, int N, int K, int splits, float* part, hipStream_t s);
+// fp16 GEMMs of token passes (M > 64; any M works), Wf in fragment order (frag_pack):
+// the epilogues of gemm() without the fp16-pair forms, on the tile shape tok_plan
+// picks, or on a given one (gemm_plan.h; N a multiple of its width, K of 64).
+// EPI_PART (gemm_tokens_tile): split-K partial sums, part[s][m][n] = the s-th of
+// `splits` equal ranges of K steps of 64 of sum_k u[m][k] W[n][k], splits * M * N
+// floats, which part_resid or resid_norm add to the residual.
+hipError_t gemm_tokens(int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo, hipStream_t s);
+hipError_t gemm_tokens_tile(int tile, int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo,
+                            int splits, hipStream_t s);
 
 // Decode GEMV with the preceding RMSNorm fused (fp16, M <= 16), on the fp16
 // copy x = hhi (+ hlo, its rounding error, when non-NULL) of the residual rows:
@@ -189,9 +189,9 @@ hipError_t rope_table(float2* tab, int cap, int dh, float theta, hipStream_t s);
 // columns stored fp32 at qkv[m][0..d) (ldo 3d), k rotated (RoPE at the token's
 // position) and v written fp16 into the paged pools.  tok_base[m] = element
 // offset of (page, head 0, slot) of token m in a layer's pool, tok_pos[m] its
-// position (tok_tables).  Any M (head_dim 64 or 128, d a multiple of 256); the
-// engine uses it where gemm_qkv_fusable(M, 3d, dh, d) holds, i.e. where gemm()
-// would take the 256 x 256-tile GEMM for the projection.
+// position (tok_tables).  Any M (head_dim 64 or 128, d a multiple of 256), on
+// 256 x 256 tiles; the engine uses it where gemm_qkv_fusable(M, 3d, dh, d) holds:
+// gemm_tokens() would take those tiles, more than one round of them.
 struct KvEpi {
   const int64_t* tok_base = nullptr;
   const int32_t* tok_pos = nullptr;
@@ -201,7 +201,7 @@ struct KvEpi {
   int d = 0, dh = 0;
 };
 bool gemm_qkv_fusable(int M, int N, int dh, int d);
-hipError_t gemm_qkv_kv(const void* u, const void* W, int M, int K, float* qkv, const KvEpi& kv, hipStream_t s);
+hipError_t gemm_qkv_kv(const void* u, const void* Wf, int M, int K, float* qkv, const KvEpi& kv, hipStream_t s);
 hipError_t tok_tables(Segs sg, KvPages kp, int H, int dh, int64_t* tok_base, int32_t* tok_pos, hipStream_t s);
 hipError_t kv_append(int ct, const float* qkv, Segs sg, int H, int dh, KvPages kp, const float2* rope,
                      void* kslab, void* vslab, hipStream_t s);

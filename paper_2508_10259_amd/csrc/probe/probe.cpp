@@ -6,10 +6,46 @@
 
 #include "kernels.h"
 
+namespace {
+
+// One thread per 16 bytes of W [N][K] (K a multiple of 32) in fragment order.
+__global__ void k_pack(const uint4* W, int N, int K, uint4* Wf) {
+  const size_t o = (size_t)blockIdx.x * blockDim.x + threadIdx.x, ks = K / 32;
+  if (o >= (size_t)N * K / 8) return;
+  const size_t l = o & 63, blk = o >> 6;
+  Wf[o] = W[((blk / ks) * 16 + (l & 15)) * (K / 8) + (blk % ks) * 4 + (l >> 4)];
+}
+
+// The row-major weights of a probe call in the order the token GEMMs read.
+struct Packed {
+  void* p = nullptr;
+  hipStream_t s;
+  Packed(const void* W, int N, int K, hipStream_t st) : s(st) {
+    if (N % 16 || K % 32 || hipMalloc(&p, (size_t)N * K * 2) != hipSuccess) return;
+    hipLaunchKernelGGL(k_pack, dim3((unsigned)(((size_t)N * K / 8 + 255) / 256)), dim3(256), 0, s, (const uint4*)W, N, K,
+                       (uint4*)p);
+  }
+  ~Packed() {
+    (void)hipStreamSynchronize(s);
+    (void)hipFree(p);
+  }
+  template <typename F> int run(F f) {
+    if (!p) return (int)hipErrorInvalidValue;
+    const hipError_t e = hipGetLastError();
+    return (int)(e == hipSuccess ? f() : e);
+  }
+};
+
+}  // namespace
+
 extern "C" {
 
 int ams_probe_gemm(int dtype, int epi, const void* u, const void* ulo, const void* W, int M, int N, int K, void* out,
                    int ldo, void* o16, void* olo, void* stream) {
+  if (dtype == ams::DT_F16 && M > 64 && !ulo && !o16 && !olo) {  // a token pass
+    Packed w(W, N, K, (hipStream_t)stream);
+    return w.run([&] { return ams::gemm_tokens(epi, u, w.p, M, N, K, out, ldo, w.s); });
+  }
   return (int)ams::gemm(dtype, epi, u, W, M, N, K, out, ldo, (hipStream_t)stream, ulo, o16, olo);
 }
 
@@ -18,14 +54,31 @@ int ams_probe_gemv_f32(int epi, const float* x, int norm, float eps, const float
   return (int)ams::gemv_f32(epi, x, norm != 0, eps, W, M, N, K, out, ldo, (hipStream_t)stream, splits, part, cnt);
 }
 
+// a token GEMM on one tile shape, weights in fragment order
+int ams_probe_gemm_tokens(int tile, int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo,
+                          int splits, void* stream) {
+  return (int)ams::gemm_tokens_tile(tile, epi, u, Wf, M, N, K, out, ldo, splits, (hipStream_t)stream);
+}
+// out[0..3]: tile, splits, weight rows on it, tile of the rest (-1: none)
+void ams_probe_tok_plan(int M, int N, int K, int split, int32_t* out) {
+  const ams::TokPlan p = ams::tok_plan(M, N, K, split != 0);
+  out[0] = p.tile; out[1] = p.splits; out[2] = p.main_n; out[3] = p.rest_tile;
+}
+size_t ams_probe_tok_part_floats(int N, int K, int T) { return ams::tok_part_floats(N, K, T); }
+
 int ams_probe_gemm_big(int epi, const void* u, const void* W, int M, int N, int K, void* out, int ldo, int bn,
                        void* stream) {
-  return (int)ams::gemm_big(epi, u, W, M, N, K, out, ldo, (hipStream_t)stream, bn);
+  const int tile = bn == 256 ? ams::TT_256x256 : bn == 128 ? ams::TT_256x128 : ams::TT_128x64;  // 192: three of 64
+  Packed w(W, N, K, (hipStream_t)stream);
+  return w.run([&] { return ams::gemm_tokens_tile(tile, epi, u, w.p, M, N, K, out, ldo, 1, w.s); });
 }
 
 int ams_probe_gemm_big_part(const void* u, const void* W, int M, int N, int K, int splits, float* part,
                             void* stream) {
-  return (int)ams::gemm_big_part(u, W, M, N, K, splits, part, (hipStream_t)stream);
+  Packed w(W, N, K, (hipStream_t)stream);
+  return w.run([&] {
+    return ams::gemm_tokens_tile(ams::TT_256x256, ams::EPI_PART, u, w.p, M, N, K, part, N, splits, w.s);
+  });
 }
 
 int ams_probe_gemm_part(const void* u, const void* ulo, const void* W, int M, int N, int K, int splits, float* part,
@@ -154,7 +207,8 @@ int ams_probe_qkv_kv(const void* u, const void* W, int K, float* qkv, const int3
   hipError_t e = ams::tok_tables(sg, kp, H, dh, tok_base, tok_pos, s);
   if (e != hipSuccess) return (int)e;
   ams::KvEpi kv{tok_base, tok_pos, kslab, vslab, (const float2*)rope, H * dh, dh};
-  return (int)ams::gemm_qkv_kv(u, W, n_tok, K, qkv, kv, s);
+  Packed w(W, 3 * H * dh, K, s);
+  return w.run([&] { return ams::gemm_qkv_kv(u, w.p, n_tok, K, qkv, kv, s); });
 }
 int ams_probe_qkv_fusable(int M, int N, int dh, int d) { return ams::gemm_qkv_fusable(M, N, dh, d) ? 1 : 0; }
 

@@ -1,0 +1,77 @@
+"""The tile shapes of the token passes' fp16 GEMMs against the exact products of their inputs."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2508_10259_amd import workload as W
+from gpu_util import log
+from test_gpu_kernels import EPI_RESID, EPI_STORE, EPI_SWIGLU, _dev, _f, _ptr, _rand, _silu, _stream, _unpack_gu, probe  # noqa: F401,E501
+
+pytestmark = pytest.mark.gpu
+EPI_PART = 3
+TILES = ((256, 256), (128, 256), (256, 128), (128, 128), (128, 128), (64, 128), (128, 64), (64, 256))
+
+
+def _frag32(Wt):
+    """MFMA fragment order of W [N][K] for any K a multiple of 32."""
+    N, K = Wt.shape
+    return np.ascontiguousarray(Wt.reshape(N // 16, 16, K // 32, 4, 8).transpose(0, 2, 3, 1, 4)).reshape(N, K)
+
+
+@pytest.mark.parametrize("tile", range(len(TILES)))
+@pytest.mark.parametrize("epi,splits", [(EPI_STORE, 1), (EPI_RESID, 1), (EPI_SWIGLU, 1), (EPI_PART, 1), (EPI_PART, 3)])
+def test_gemm_tokens_tile(probe, tile, epi, splits):  # noqa: F811
+    """Token counts around the tile's edges, fewer K steps than the kernels' slots and stages (64,
+    128, 192) and more (576), splits of unequal lengths."""
+    import torch
+    bm, bn = TILES[tile]
+    N = 3 * bn
+    for M, K in ((1, 64), (bm - 1, 128), (bm, 192), (bm + 1, 576), (2 * bm + 17, 448), (9 * bm + 5, 256)):
+        if splits > K // 64:
+            continue
+        log(f"gemm_tokens tile={TILES[tile]} epi={epi} splits={splits} M={M} N={N} K={K}")
+        u, Wt = _rand((M, K), 111, M, K), _rand((N, K), 112, N, K, std=0.05)
+        h0 = W.random_gaussian((M, N), 113, M, dtype="f32")
+        y = _f(u, "f16") @ _f(Wt, "f16").T
+        ldo = N // 2 if epi == EPI_SWIGLU else N
+        if epi == EPI_SWIGLU:
+            g, up = _unpack_gu(y.T, N // 2)
+            ref = (_silu(g) * up).T
+            out = torch.full((M, ldo), float("nan"), dtype=torch.float16, device="cuda")
+        elif epi == EPI_RESID:
+            ref, out = h0 + y, torch.from_numpy(h0.copy()).cuda()
+        else:
+            ref, out = y, torch.full((splits, M, N), float("nan"), device="cuda")
+        ud, wd = _dev(u, "f16"), _dev(_frag32(Wt), "f16")
+        assert probe.ams_probe_gemm_tokens(tile, epi, _ptr(ud), _ptr(wd), M, N, K, _ptr(out), ldo, splits,
+                                           _stream()) == 0
+        torch.cuda.synchronize()
+        got = out.float().cpu().numpy().astype(np.float64)
+        if epi == EPI_PART:
+            for s in range(splits):  # a split holds its own range of K steps
+                k0, k1 = s * (K // 64) // splits * 64, (s + 1) * (K // 64) // splits * 64
+                part = _f(u[:, k0:k1], "f16") @ _f(Wt[:, k0:k1], "f16").T
+                assert np.max(np.abs(got[s] - part)) <= 2e-5 * max(1.0, np.max(np.abs(part))) * np.sqrt(K / 64), s
+            continue
+        got = got.reshape(ref.shape)
+        scale = max(1.0, float(np.max(np.abs(ref))))
+        tol = 2e-5 * scale * np.sqrt(K / 64)  # fp16 products are exact in the fp32 accumulator
+        if epi == EPI_SWIGLU:
+            tol = max(tol, 2 ** -11 * scale)  # the fp16 output
+        assert float(np.max(np.abs(got - ref))) <= tol
+
+
+def test_gemm_tokens_refusals(probe):  # noqa: F811
+    import torch
+    x = torch.zeros(1 << 20, dtype=torch.float16, device="cuda")
+    out = torch.zeros(1 << 20, device="cuda")
+
+    def call(tile, epi, M, N, K, splits):
+        return probe.ams_probe_gemm_tokens(tile, epi, _ptr(x), _ptr(x), M, N, K, _ptr(out), N, splits, _stream())
+
+    assert call(0, EPI_STORE, 8, 128, 64, 1) != 0   # N not a multiple of the tile width
+    assert call(5, EPI_STORE, 8, 128, 96, 1) != 0   # K not a multiple of 64
+    assert call(5, EPI_STORE, 8, 128, 128, 2) != 0  # splits without partial sums
+    assert call(5, EPI_PART, 8, 128, 128, 3) != 0   # more splits than K steps
+    assert call(8, EPI_STORE, 8, 128, 128, 1) != 0
