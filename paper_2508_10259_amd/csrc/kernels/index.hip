@@ -10,13 +10,16 @@
 //                    little-endian units of B_i zero-padded to s bytes;
 //   HashFunc2(h_1..h_k) = (sum_i h_i q^(k-i)) q + N.
 //
-// Phase 1: one workgroup of 256 threads per segment.  Each thread evaluates
-// the polynomial of 8 consecutive units (one 16-byte load) and the 256 pieces
-// are combined pairwise in order (left * base^len(right) + right) through wave
-// shuffles and LDS; a segment of fewer than 2048 units is right-aligned so
-// that the idle leading threads contribute the polynomial's leading zeros, and
-// longer segments go block by block.  The work is integer ALU on data read once
-// from HBM.
+// Phase 1: a group of G lanes per segment (G = 64, or the power of two that
+// holds a shorter segment's 16-byte chunks).  HashFunc1 is a dot product of
+// the units with powers of r, and a 16-bit unit times a 31-bit power leaves 17
+// bits of headroom in 64: a lane keeps the 8 powers of its place in a round of G
+// chunks per base in registers, sums its 8 products without reducing, folds
+// rounds with one multiplication by r^(8 G) each, and the group adds the lanes'
+// residues.  Bound by HBM and the 64-bit multiply-adds (16 per 16 bytes)
+// alike; with a Horner chain per 16 bytes and a tree of modular products per
+// segment it was bound by integer ALU: 157 MB in 4 KB segments 209 -> 38 us.
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -47,120 +50,137 @@ __device__ uint64_t powm(uint64_t b, uint64_t e) {
   return r;
 }
 
-// In-order combination of the 256 threads' (value, piece) pairs of one block:
-// value(left ++ right) = value(left) * base^len(right) + value(right); at level l
-// every piece spans 8 * 2^l units.  pw[l] = base^(8 * 2^l).  Returns the
-// block's value in thread 0.
-__device__ uint64_t tree256(uint64_t v, const uint64_t* pw, uint64_t* lds) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int l = 0; l < 6; ++l) {
-    const int w = 1 << l;
-    const uint64_t right = (uint64_t)__shfl_down((unsigned long long)v, w, 64);
-    if ((lane & (2 * w - 1)) == 0) v = addm(mulm(v, pw[l]), right);
-  }
-  if (lane == 0) lds[wave] = v;
-  __syncthreads();
-  uint64_t out = 0;
-  if (threadIdx.x == 0) {
-    const uint64_t a = addm(mulm(lds[0], pw[6]), lds[1]);
-    const uint64_t b = addm(mulm(lds[2], pw[6]), lds[3]);
-    out = addm(mulm(a, pw[7]), b);
-  }
-  __syncthreads();
-  return out;
+__host__ __device__ constexpr uint64_t pow31(uint64_t b, uint64_t e) {  // b^e mod 2^31 - 1
+  uint64_t r = 1;
+  for (b %= M31; e; e >>= 1, b = b * b % M31)
+    if (e & 1) r = r * b % M31;
+  return r;
 }
 
-__device__ __forceinline__ uint64_t horner8(const uint32_t (&w)[4], uint64_t base) {
-  uint64_t v = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    v = addm(mulm(v, base), w[i] & 0xFFFFu);
-    v = addm(mulm(v, base), w[i] >> 16);
-  }
-  return v;
+// a + b mod 2^31 - 1 as a value <= 2^31 - 1, for such a and b
+__device__ __forceinline__ uint32_t fold_add(uint32_t a, uint32_t b) {
+  const uint32_t t = a + b;
+  return (t & (uint32_t)M31) + (t >> 31);
 }
 
-// Phase 1.  Segment g = blockIdx.x covers bytes [g s, g s + s) of data (zero
-// beyond n_bytes).  s is a multiple of 16 and data is 16-byte aligned.
+// Phase 1.  Segment g covers bytes [g s, g s + s) of data (zero beyond
+// n_bytes); s is a multiple of 16 and data is 16-byte aligned.  A segment's
+// C = s / 16 chunks sit right-aligned in its R rounds of G, so that the lanes
+// before its start contribute the polynomial's leading zeros.  m0 / m1 =
+// r^(8 G) of the two bases.
 __global__ __launch_bounds__(256) void k_hash_segments(const uint8_t* __restrict__ data, uint64_t n_bytes, int s,
+                                                       uint64_t k, int G, uint32_t m0, uint32_t m1,
                                                        uint64_t* __restrict__ seg_out) {
-  __shared__ uint64_t lds[2][4];
-  __shared__ uint64_t pws[2][8];
-  const uint64_t g = blockIdx.x;
-  const uint64_t base = g * (uint64_t)s;
-  const int U = s / 2, nblk = (U + 2047) / 2048;
-  if (threadIdx.x < 2) {
-    const uint64_t r = threadIdx.x == 0 ? HR0 : HR1;
-    uint64_t p = powm(r, 8);
-    for (int l = 0; l < 8; ++l) {
-      pws[threadIdx.x][l] = p;
-      p = mulm(p, p);
+  const int lane = threadIdx.x & 63, gl = lane & (G - 1), per = 64 / G;
+  const int C = s / 16, R = (C + G - 1) / G, lead = R * G - C;
+  uint32_t w0[8], w1[8];  // unit i of the lane's chunk in a segment's last round: r^(8 (G - gl) - i)
+  {
+    uint64_t a = powm(HR0, 8 * (G - gl) - 7), b = powm(HR1, 8 * (G - gl) - 7);
+#pragma unroll
+    for (int i = 7; i >= 0; --i) {
+      w0[i] = (uint32_t)a;
+      w1[i] = (uint32_t)b;
+      a = mulm(a, HR0);
+      b = mulm(b, HR1);
     }
   }
-  __syncthreads();
-  uint64_t acc0 = 0, acc1 = 0;  // thread 0: the segment's value so far
-  for (int b = 0; b < nblk; ++b) {
-    const int units = min(2048, U - b * 2048);  // a multiple of 8
-    const int chunks = units / 8;
-    const int c = (int)threadIdx.x - (256 - chunks);  // right-aligned
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-    if (c >= 0) {
-      const uint64_t off = base + 2ull * (b * 2048 + 8 * c);  // byte offset of the thread's 16 bytes
-      if (off + 16 <= n_bytes) {
-        const uint4 q = *reinterpret_cast<const uint4*>(data + off);
-        w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
-      } else if (off < n_bytes) {
-        for (uint64_t i = off; i < n_bytes; ++i) w[(i - off) >> 2] |= (uint32_t)data[i] << (8 * ((i - off) & 3));
+  const uint64_t wave = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6), waves = (uint64_t)gridDim.x * 4;
+  for (uint64_t g0 = wave * per; g0 < k; g0 += waves * per) {
+    const uint64_t g = g0 + lane / G, base = g * (uint64_t)s;
+    uint64_t a0 = 0, a1 = 0;
+    for (int rd = 0; rd < R; rd += 4) {
+      uint4 q[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int c = (rd + x) * G + gl - lead;
+        q[x] = uint4{0u, 0u, 0u, 0u};
+        if (rd + x < R && c >= 0 && g < k) {
+          const uint64_t off = base + 16ull * c;
+          if (off + 16 <= n_bytes) {
+            q[x] = *reinterpret_cast<const uint4*>(data + off);
+          } else if (off < n_bytes) {  // the input's last bytes
+            uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int i = 0; i < 15; ++i)
+              if (off + i < n_bytes) w[i >> 2] |= (uint32_t)data[off + i] << (8 * (i & 3));
+            q[x] = uint4{w[0], w[1], w[2], w[3]};
+          }
+        }
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        if (rd + x >= R) break;
+        if (rd + x > 0) {  // residues < 2^31 times m < 2^31, plus 8 products < 2^47: below 2^63
+          a0 = red(a0) * m0;
+          a1 = red(a1) * m1;
+        }
+        const uint32_t u[4] = {q[x].x, q[x].y, q[x].z, q[x].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t lo = u[i] & 0xFFFFu, hi = u[i] >> 16;
+          a0 += (uint64_t)lo * w0[2 * i];
+          a0 += (uint64_t)hi * w0[2 * i + 1];
+          a1 += (uint64_t)lo * w1[2 * i];
+          a1 += (uint64_t)hi * w1[2 * i + 1];
+        }
       }
     }
-    const uint64_t v0 = tree256(horner8(w, HR0), pws[0], lds[0]);
-    const uint64_t v1 = tree256(horner8(w, HR1), pws[1], lds[1]);
-    if (threadIdx.x == 0) {  // Horner over blocks: acc r^units + block
-      acc0 = addm(mulm(acc0, powm(HR0, units)), v0);
-      acc1 = addm(mulm(acc1, powm(HR1, units)), v1);
+    uint32_t v0 = (uint32_t)red(a0), v1 = (uint32_t)red(a1);
+    for (int o = 1; o < G; o <<= 1) {
+      v0 = fold_add(v0, __shfl_xor(v0, o, 64));
+      v1 = fold_add(v1, __shfl_xor(v1, o, 64));
     }
-  }
-  if (threadIdx.x == 0) {
-    const uint64_t len = n_bytes - base < (uint64_t)s ? n_bytes - base : (uint64_t)s;
-    const uint64_t h0 = addm(mulm(acc0, HR0), red(len));
-    const uint64_t h1 = addm(mulm(acc1, HR1), red(len));
-    seg_out[g] = h0 | (h1 << 32);
+    if (gl == 0 && g < k) {
+      const uint64_t len = n_bytes - base < (uint64_t)s ? n_bytes - base : (uint64_t)s;
+      seg_out[g] = red((uint64_t)v0 + len) | (red((uint64_t)v1 + len) << 32);
+    }
   }
 }
 
-// Phase 2 over k segment hashes: 256 threads, thread t merging the virtual
-// range [t m, t m + m) of a right-aligned index space (m = ceil(k / 256)), then
-// the in-order tree with q^(m 2^l).  out = (value) q + n_bytes per component.
-__global__ __launch_bounds__(256) void k_hash_merge(const uint64_t* __restrict__ seg, uint64_t k, uint64_t n_bytes,
-                                                    uint64_t* __restrict__ out) {
-  __shared__ uint64_t lds[2][4];
-  __shared__ uint64_t pws[2][8];
-  const uint64_t m = (k + 255) / 256, lead = 256 * m - k;
-  if (threadIdx.x < 2) {
-    const uint64_t q = threadIdx.x == 0 ? HQ0 : HQ1;
-    uint64_t p = powm(q, m);
-    for (int l = 0; l < 8; ++l) {
-      pws[threadIdx.x][l] = p;
-      p = mulm(p, p);
+// Phase 2 over k segment hashes, one workgroup: thread t runs Horner over
+// segments t, t + 1024, ... of a right-aligned index space (neighbouring threads
+// read neighbouring hashes; qn0 / qn1 = q^1024 of the two bases), its sum is
+// then worth q^(1024 - t), and the residues are added.  H = sum + n_bytes per
+// component.  (A contiguous range per thread of 256 read 8 bytes per cache line
+// and step: 55 -> 17 us for 38,400 segments, most of it one CU's 307 KB of loads.)
+constexpr int MERGE_T = 1024;
+__global__ __launch_bounds__(MERGE_T) void k_hash_merge(const uint64_t* __restrict__ seg, uint64_t k, uint64_t n_bytes,
+                                                        uint32_t qn0, uint32_t qn1, uint64_t* __restrict__ out) {
+  __shared__ uint32_t s0[MERGE_T / 64], s1[MERGE_T / 64];
+  const int t = threadIdx.x;
+  const uint64_t m = (k + MERGE_T - 1) / MERGE_T, lead = MERGE_T * m - k;
+  uint64_t a0 = 0, a1 = 0;
+  for (uint64_t j = 0; j < m; j += 8) {
+    uint64_t h[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const uint64_t vi = (j + x) * MERGE_T + t;
+      h[x] = j + x < m && vi >= lead ? seg[vi - lead] : 0ull;
+    }
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      if (j + x >= m) break;
+      a0 = red(a0) * qn0 + (h[x] & 0xFFFFFFFFull);
+      a1 = red(a1) * qn1 + (h[x] >> 32);
     }
   }
-  __syncthreads();
-  uint64_t v0 = 0, v1 = 0;
-  for (uint64_t j = 0; j < m; ++j) {
-    const uint64_t vi = threadIdx.x * m + j;
-    const uint64_t h = vi >= lead ? seg[vi - lead] : 0ull;
-    v0 = addm(mulm(v0, HQ0), h & 0xFFFFFFFFull);
-    v1 = addm(mulm(v1, HQ1), h >> 32);
+  uint32_t v0 = (uint32_t)mulm(red(a0), powm(HQ0, MERGE_T - t)), v1 = (uint32_t)mulm(red(a1), powm(HQ1, MERGE_T - t));
+  for (int o = 1; o < 64; o <<= 1) {
+    v0 = fold_add(v0, __shfl_xor(v0, o, 64));
+    v1 = fold_add(v1, __shfl_xor(v1, o, 64));
   }
-  // tree256 assumes pieces of 8 * 2^l units; here a piece at level l spans m 2^l
-  // segments, which pws already encodes (pws[l] = q^(m 2^l))
-  const uint64_t t0 = tree256(v0, pws[0], lds[0]);
-  const uint64_t t1 = tree256(v1, pws[1], lds[1]);
-  if (threadIdx.x == 0) {
-    const uint64_t H0 = addm(mulm(t0, HQ0), red(n_bytes % M31));
-    const uint64_t H1 = addm(mulm(t1, HQ1), red(n_bytes % M31));
-    out[0] = H0 | (H1 << 32);
+  if ((t & 63) == 0) {
+    s0[t >> 6] = v0;
+    s1[t >> 6] = v1;
+  }
+  __syncthreads();
+  if (t == 0) {
+    uint64_t h0 = red(n_bytes % M31), h1 = h0;
+    for (int w = 0; w < MERGE_T / 64; ++w) {
+      h0 = addm(h0, s0[w]);
+      h1 = addm(h1, s1[w]);
+    }
+    out[0] = h0 | (h1 << 32);
   }
 }
 
@@ -218,12 +238,18 @@ hipError_t index_noalloc_scratch(int device, uint64_t** ptr) {
 hipError_t hash_segments(const void* data, uint64_t n_bytes, int s, uint64_t* seg_out, hipStream_t st) {
   const uint64_t k = (n_bytes + s - 1) / s;
   if (k == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_hash_segments, dim3((unsigned)k), dim3(256), 0, st, (const uint8_t*)data, n_bytes, s, seg_out);
+  int G = 64;
+  while (G > 1 && G / 2 >= s / 16) G /= 2;
+  const uint64_t per_wg = 4 * (64 / G);  // segments of a workgroup's pass
+  const uint64_t wgs = std::min<uint64_t>((k + per_wg - 1) / per_wg, 2048);  // 8 per CU resident
+  hipLaunchKernelGGL(k_hash_segments, dim3((unsigned)wgs), dim3(256), 0, st, (const uint8_t*)data, n_bytes, s, k, G,
+                     (uint32_t)pow31(HR0, 8 * G), (uint32_t)pow31(HR1, 8 * G), seg_out);
   return hipGetLastError();
 }
 
 hipError_t hash_merge(const uint64_t* seg, uint64_t k, uint64_t n_bytes, uint64_t* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_hash_merge, dim3(1), dim3(256), 0, st, seg, k, n_bytes, out);
+  constexpr uint32_t q0 = (uint32_t)pow31(HQ0, MERGE_T), q1 = (uint32_t)pow31(HQ1, MERGE_T);
+  hipLaunchKernelGGL(k_hash_merge, dim3(1), dim3(MERGE_T), 0, st, seg, k, n_bytes, q0, q1, out);
   return hipGetLastError();
 }
 

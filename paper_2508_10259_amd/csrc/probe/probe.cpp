@@ -220,6 +220,14 @@ int ams_probe_attn_prefill(int ct, const float* qkv, const int32_t* row, const i
                                 (hipStream_t)stream);
 }
 
+// one flow embedding of the latents x into h, then the readout of h into x
+int ams_probe_flow(int st, float* x, const void* w_in, const void* w_t, const void* w_out, float tau, float eps, float dt,
+                   int n_tok, int a, int d, float* h, void* stream) {
+  hipError_t e = ams::flow_embed(st, x, w_in, w_t, tau, n_tok, a, d, h, (hipStream_t)stream);
+  if (e == hipSuccess) e = ams::flow_update(st, h, w_out, eps, dt, n_tok, a, d, x, (hipStream_t)stream);
+  return (int)e;
+}
+
 int ams_probe_stream_copy(const void* src, void* dst, size_t bytes, int grid, void* stream) {
   return (int)ams::stream_copy(src, dst, bytes, grid, (hipStream_t)stream);
 }
