@@ -40,14 +40,17 @@ __device__ __forceinline__ uint64_t red(uint64_t x) {  // x < 2^63 -> x mod (2^3
 }
 __device__ __forceinline__ uint64_t mulm(uint64_t a, uint64_t b) { return red(a * b); }  // a, b < 2^31
 __device__ __forceinline__ uint64_t addm(uint64_t a, uint64_t b) { return red(a + b); }
-__device__ uint64_t powm(uint64_t b, uint64_t e) {
-  uint64_t r = 1;
-  while (e) {
-    if (e & 1) r = mulm(r, b);
-    b = mulm(b, b);
-    e >>= 1;
+// b0^e and b1^e, the two chains side by side
+__device__ __forceinline__ void powm2(uint64_t b0, uint64_t b1, uint32_t e, uint64_t& r0, uint64_t& r1) {
+  r0 = r1 = 1;
+  for (; e; e >>= 1) {
+    if (e & 1) {
+      r0 = mulm(r0, b0);
+      r1 = mulm(r1, b1);
+    }
+    b0 = mulm(b0, b0);
+    b1 = mulm(b1, b1);
   }
-  return r;
 }
 
 __host__ __device__ constexpr uint64_t pow31(uint64_t b, uint64_t e) {  // b^e mod 2^31 - 1
@@ -75,7 +78,8 @@ __global__ __launch_bounds__(256) void k_hash_segments(const uint8_t* __restrict
   const int C = s / 16, R = (C + G - 1) / G, lead = R * G - C;
   uint32_t w0[8], w1[8];  // unit i of the lane's chunk in a segment's last round: r^(8 (G - gl) - i)
   {
-    uint64_t a = powm(HR0, 8 * (G - gl) - 7), b = powm(HR1, 8 * (G - gl) - 7);
+    uint64_t a, b;
+    powm2(HR0, HR1, 8 * (G - gl) - 7, a, b);
 #pragma unroll
     for (int i = 7; i >= 0; --i) {
       w0[i] = (uint32_t)a;
@@ -137,24 +141,25 @@ __global__ __launch_bounds__(256) void k_hash_segments(const uint8_t* __restrict
   }
 }
 
-// Phase 2 over k segment hashes, one workgroup: thread t runs Horner over
-// segments t, t + 1024, ... of a right-aligned index space (neighbouring threads
-// read neighbouring hashes; qn0 / qn1 = q^1024 of the two bases), its sum is
-// then worth q^(1024 - t), and the residues are added.  H = sum + n_bytes per
+// Phase 2 over k segment hashes, one workgroup of T threads: thread t runs
+// Horner over segments t, t + T, ... of a right-aligned index space (neighbouring
+// threads read neighbouring hashes; qn0 / qn1 = q^T of the two bases), its sum is
+// then worth q^(T - t), and the residues are added.  H = sum + n_bytes per
 // component.  (A contiguous range per thread of 256 read 8 bytes per cache line
 // and step: 55 -> 17 us for 38,400 segments, most of it one CU's 307 KB of loads.)
-constexpr int MERGE_T = 1024;
-__global__ __launch_bounds__(MERGE_T) void k_hash_merge(const uint64_t* __restrict__ seg, uint64_t k, uint64_t n_bytes,
-                                                        uint32_t qn0, uint32_t qn1, uint64_t* __restrict__ out) {
-  __shared__ uint32_t s0[MERGE_T / 64], s1[MERGE_T / 64];
-  const int t = threadIdx.x;
-  const uint64_t m = (k + MERGE_T - 1) / MERGE_T, lead = MERGE_T * m - k;
+constexpr int MERGE_MAX_T = 1024;
+__global__ __launch_bounds__(MERGE_MAX_T) void k_hash_merge(const uint64_t* __restrict__ seg, uint64_t k,
+                                                            uint64_t n_bytes, uint32_t qn0, uint32_t qn1,
+                                                            uint64_t* __restrict__ out) {
+  __shared__ uint32_t s0[MERGE_MAX_T / 64], s1[MERGE_MAX_T / 64];
+  const int t = threadIdx.x, T = blockDim.x;
+  const uint64_t m = (k + T - 1) / T, lead = T * m - k;
   uint64_t a0 = 0, a1 = 0;
   for (uint64_t j = 0; j < m; j += 8) {
     uint64_t h[8];
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-      const uint64_t vi = (j + x) * MERGE_T + t;
+      const uint64_t vi = (j + x) * T + t;
       h[x] = j + x < m && vi >= lead ? seg[vi - lead] : 0ull;
     }
 #pragma unroll
@@ -164,7 +169,9 @@ __global__ __launch_bounds__(MERGE_T) void k_hash_merge(const uint64_t* __restri
       a1 = red(a1) * qn1 + (h[x] >> 32);
     }
   }
-  uint32_t v0 = (uint32_t)mulm(red(a0), powm(HQ0, MERGE_T - t)), v1 = (uint32_t)mulm(red(a1), powm(HQ1, MERGE_T - t));
+  uint64_t p0, p1;
+  powm2(HQ0, HQ1, T - t, p0, p1);
+  uint32_t v0 = (uint32_t)mulm(red(a0), p0), v1 = (uint32_t)mulm(red(a1), p1);
   for (int o = 1; o < 64; o <<= 1) {
     v0 = fold_add(v0, __shfl_xor(v0, o, 64));
     v1 = fold_add(v1, __shfl_xor(v1, o, 64));
@@ -176,7 +183,7 @@ __global__ __launch_bounds__(MERGE_T) void k_hash_merge(const uint64_t* __restri
   __syncthreads();
   if (t == 0) {
     uint64_t h0 = red(n_bytes % M31), h1 = h0;
-    for (int w = 0; w < MERGE_T / 64; ++w) {
+    for (int w = 0; w < T / 64; ++w) {
       h0 = addm(h0, s0[w]);
       h1 = addm(h1, s1[w]);
     }
@@ -248,8 +255,10 @@ hipError_t hash_segments(const void* data, uint64_t n_bytes, int s, uint64_t* se
 }
 
 hipError_t hash_merge(const uint64_t* seg, uint64_t k, uint64_t n_bytes, uint64_t* out, hipStream_t st) {
-  constexpr uint32_t q0 = (uint32_t)pow31(HQ0, MERGE_T), q1 = (uint32_t)pow31(HQ1, MERGE_T);
-  hipLaunchKernelGGL(k_hash_merge, dim3(1), dim3(MERGE_T), 0, st, seg, k, n_bytes, q0, q1, out);
+  int T = 64;  // few segments: few waves to start and join
+  while (T < MERGE_MAX_T && (uint64_t)T < k) T *= 2;
+  hipLaunchKernelGGL(k_hash_merge, dim3(1), dim3(T), 0, st, seg, k, n_bytes, (uint32_t)pow31(HQ0, T),
+                     (uint32_t)pow31(HQ1, T), out);
   return hipGetLastError();
 }
 
