@@ -27,6 +27,16 @@ static bool fused_norm(const Ctx& c, int rows) { return c.model->ct == DT_F16 &&
 // fp32 passes of up to 64 tokens run gemv_f32, which applies the RMSNorm itself.
 static bool short_f32(const Model& md, int M) { return md.ct == DT_F32 && M <= 64; }
 
+// Projections (N x K) of an fp16 token pass of up to 64 tokens that run the wide
+// GEMM: from 10 M weights on (4 M for the residual ones, whose K is split), where
+// the weight stream sets the pace (7B, 16 tokens: QKV 30.6 -> 20.0 us, gate|up 47.0
+// -> 32.0, down with the norm 30.0 -> 21.9; 64 tokens: 70.5 -> 26.3, 114 -> 39, 69 ->
+// 28.5).  Below, the skinny GEMV's single launch wins (d = 1024, 16 tokens: QKV 5.0
+// against 6.9 us, gate|up 6.4 against 8.9).
+static bool short_wide(const Model& md, int M, int N, int K, bool resid) {
+  return md.ct == DT_F16 && M <= 64 && (size_t)N * K >= (resid ? 4000000u : 10000000u);
+}
+
 // fp16 token passes longer than that run gemm_tokens on the fragment-ordered weights.
 static bool tiled_f16(const Model& md, int M) { return md.ct == DT_F16 && M > 64; }
 
@@ -309,6 +319,16 @@ static hipError_t tokens_resid(Ctx& c, const void* x, const void* W, const void*
   const int d = md.cfg.d_model;
   normed = false;
   if (short_f32(md, M)) return resid_f32(c, x, W, M, K, c.h(), s);
+  if (short_wide(md, M, d, K, true)) {
+    const int S = decode_wsplit(d, K);
+    if (wide_fused_reduce(M))
+      return gemm_wide_reduce(EPI_RESID, x, nullptr, Wf, M, d, K, S, c.kpart(), c.wcnt(), nullptr, nullptr, 0, c.h(),
+                              nullptr, nullptr, nullptr, nullptr, 0.f, s);
+    hipError_t e = gemm_wide(x, nullptr, Wf, M, d, K, S, c.kpart(), s);
+    if (e == hipSuccess) e = resid_norm(c.kpart(), S, M, d, c.h(), md.cfg.rms_eps, c.u(), s);
+    normed = e == hipSuccess;
+    return e;
+  }
   if (tiled_f16(md, M)) {
     const TokPlan p = tok_plan(M, d, K, true);
     if (p.splits == 1) return gemm_tokens_tile(p.tile, EPI_RESID, x, Wf, M, d, K, c.h(), d, 1, s);
@@ -318,6 +338,19 @@ static hipError_t tokens_resid(Ctx& c, const void* x, const void* W, const void*
     return e;
   }
   return gemm(md.ct, EPI_RESID, x, W, M, d, K, c.h(), d, s);
+}
+
+// A projection of u on the wide GEMM (short_wide).
+static hipError_t short_proj(const Ctx& c, int epi, const void* Wf, int M, int N, int K, void* out, int ldo,
+                             hipStream_t s) {
+  const int S = decode_wsplit(N, K);
+  if (epi == EPI_SWIGLU ? S == 1 : wide_fused_reduce(M))
+    return gemm_wide_reduce(epi, c.u(), nullptr, Wf, M, N, K, S, c.kpart(), c.wcnt(), out, nullptr, ldo, nullptr,
+                            nullptr, nullptr, nullptr, nullptr, 0.f, s);
+  hipError_t e = gemm_wide(c.u(), nullptr, Wf, M, N, K, S, c.kpart(), s);
+  if (e != hipSuccess) return e;
+  if (epi == EPI_SWIGLU) return part_swiglu(c.kpart(), S, M, N, out, nullptr, s);
+  return part_store(c.kpart(), S, M, N, (float*)out, s);
 }
 
 // One decoder layer over the M tokens of a token pass; u_ready: u already holds
@@ -340,6 +373,8 @@ static hipError_t layer_tokens(Ctx& c, int l, int M, const Segs& sg, hipStream_t
   } else {
     if (f32s)
       TRY(gemv_f32(EPI_STORE, c.h(), true, m.rms_eps, (const float*)md.wqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
+    else if (short_wide(md, M, 3 * d, d, false))
+      TRY(short_proj(c, EPI_STORE, md.fqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
     else if (tiled)
       TRY(gemm_tokens(EPI_STORE, c.u(), md.fqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
     else
@@ -356,6 +391,8 @@ static hipError_t layer_tokens(Ctx& c, int l, int M, const Segs& sg, hipStream_t
   if (!u_ready && !f32s) TRY(rmsnorm(dt, c.h(), M, d, m.rms_eps, c.u(), s));
   if (f32s)
     TRY(gemv_f32(EPI_SWIGLU, c.h(), true, m.rms_eps, (const float*)md.wgu(l), M, 2 * F, d, (float*)c.a(), F, s));
+  else if (short_wide(md, M, 2 * F, d, false))
+    TRY(short_proj(c, EPI_SWIGLU, md.fgu(l), M, 2 * F, d, c.a(), F, s));
   else if (tiled)
     TRY(gemm_tokens(EPI_SWIGLU, c.u(), md.fgu(l), M, 2 * F, d, c.a(), F, s));
   else
@@ -504,12 +541,8 @@ static hipError_t norm_proj(const Rows& g, int epi, const float* h, const void* 
       TRY(rmsnorm(md.ct, h, g.n, K, eps, g.u(), s, ulo));
     }
     if (wide) {  // partial sums of 128-row tiles, then the epilogue
-      // When the attention adds the partial sums, every split costs each of its
-      // workgroups another read of its q, k, v slices: two splits measured
-      // best on the 7B decoder at 64 rows (decode 47.2 / 45.9 / 45.0 / 44.8 ms
-      // per step at 8 / 4 / 5 / 2 splits).
-      const int splits = defer ? std::max(1, std::min(2, K >> 7)) : decode_wsplit(N, K);
-      if (!defer && wide_fused_reduce(g.n)) {
+      const int splits = decode_wsplit(N, K);
+      if (epi == EPI_SWIGLU ? splits == 1 : !defer && wide_fused_reduce(g.n)) {
         TRY(gemm_wide_reduce(epi, g.u(), ulo, Wf, g.n, N, K, splits, g.c->kpart(), g.c->wcnt(), out, olo, ldo, nullptr,
                              nullptr, nullptr, nullptr, ss, eps, s));
       } else {

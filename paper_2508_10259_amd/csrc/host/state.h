@@ -144,22 +144,17 @@ inline int decode_ksplit(int N, int K) {
   return std::max(1, s);
 }
 
-// K splits of a wide decode GEMM (more than 8 rows; 128 weight rows per
-// workgroup, at least 4 chunks of 128 per split, at most 16 splits).  The time
-// model is the rounds of workgroups per CU over the work per workgroup,
-// ceil(tiles * S / 256) / S on the 256 CUs; every further split also adds
-// partial sums and staging, so the smallest S within 5% of the model's minimum
-// is taken.  On the 7B shapes at 16 and 64 rows this is the measured best of
-// S = 1..8 (QKV 8, gate|up 4, O and down 8); counts that leave the last round
-// of workgroups mostly empty lose to both neighbours.
+// K splits of a wide GEMM (128 weight rows per workgroup; at least 2 chunks of
+// 128 per split, at most 8 splits): about 192 workgroups.  That many stream the
+// weights as fast as 256 or 384 do, and every further split adds partial sums.
+// Measured with 9 to 64 rows against the former rule (the smallest of 16 within 5%
+// of the best ratio of work to rounds of 256), us per projection with its reduction:
+// 7B gate|up 4 -> 1 splits 36 -> 31 at 9 rows, 52 -> 49 at 64; O 8 -> 6 12.0 ->
+// 11.2 and 19.9 -> 17.6; down 8 -> 6 18.7 -> 18.8 and 32.2 -> 29.1; d = 2048 QKV 2 -> 4
+// 8.7 -> 7.5 and 13.5 -> 10.3; d = 1024 O 2 -> 4 8.0 -> 6.5 and 11.0 -> 9.9.
 inline int decode_wsplit(int N, int K) {
-  const int tiles = std::max(N / 128, 1), smax = std::max(1, std::min(16, (K / 128) / 4));
-  auto t = [&](int s) { return (double)((tiles * s + 255) / 256) / s; };
-  double best = t(1);
-  for (int s = 2; s <= smax; ++s) best = std::min(best, t(s));
-  int s = 1;
-  while (t(s) > 1.05 * best) ++s;
-  return s;
+  const int tiles = std::max(N / 128, 1);
+  return std::max(1, std::min({(2 * 192 + tiles) / (2 * tiles), (K / 128) / 2, 8}));
 }
 
 // Persistent decode (one launch per step) applies up to this many rows.
@@ -261,9 +256,12 @@ inline CtxLayout ctx_layout(const Cfg& c, int batch, int capacity, int pass_toke
                    decode_wsplit(2 * (int)F, (int)d) * B * 2 * F, decode_wsplit((int)d, (int)F) * B * d,
                    decode_wsplit((int)NB, (int)d) * B * NB});
   }
-  if (es == 2)
+  if (es == 2) {  // token passes of up to 64 tokens, and longer ones
+    const size_t m = std::min<size_t>(T, 64);
+    kp = std::max({kp, decode_wsplit(3 * (int)d, (int)d) * m * 3 * d, decode_wsplit((int)d, (int)d) * m * d,
+                   decode_wsplit(2 * (int)F, (int)d) * m * 2 * F, decode_wsplit((int)d, (int)F) * m * d});
     kp = std::max({kp, tok_part_floats((int)d, (int)d, x.pass_tokens), tok_part_floats((int)d, (int)F, x.pass_tokens)});
-  else kp = std::max(kp, (size_t)std::max(f32_split((int)d, (int)d), f32_split((int)d, (int)F)) * std::min<size_t>(T, 64) * d);
+  } else kp = std::max(kp, (size_t)std::max(f32_split((int)d, (int)d), f32_split((int)d, (int)F)) * std::min<size_t>(T, 64) * d);
   x.kpart = o; o = align256(o + kp * 4);
   x.part = o; o = align256(o + B * (size_t)c.n_heads * x.max_splits * (c.head_dim + 2) * 4);
   x.logits = o; o = align256(o + B * (size_t)bins_padded(c) * 4);

@@ -365,20 +365,26 @@ struct WideEpi {
   float eps;
 };
 
+// 1/rms of each of M input rows from their sums of squares per 128 columns, as
+// row_rstd computes it (1 when ss is NULL), into rs; eight waves, no barrier.
+__device__ __forceinline__ void wide_rstd(const float* ss, int M, int K, float eps, float* rs) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nss = K / 128;
+  for (int m = wave; m < M; m += 8) {
+    float t = 0.f;
+    if (ss)
+      for (int k = lane; k < nss; k += 64) t += ss[(size_t)m * nss + k];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    if (lane == 0) rs[m] = ss ? 1.0f / sqrtf(t * (1.0f / (float)K) + eps) : 1.f;
+  }
+}
+
 template <int EPI>
 __device__ void wide_reduce(const WideEpi& e, __amdgpu_buffer_rsrc_t pr, int S, int M, int N, int K, int n0) {
   __shared__ float rs[64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if constexpr (EPI != EPI_RESID) {  // 1/rms of each input row, as row_rstd computes it
-    const int nss = K / 128;
-    for (int m = wave; m < M; m += 8) {
-      float t = 0.f;
-      if (e.ss_in)
-        for (int k = lane; k < nss; k += 64) t += e.ss_in[(size_t)m * nss + k];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-      if (lane == 0) rs[m] = e.ss_in ? 1.0f / sqrtf(t * (1.0f / (float)K) + e.eps) : 1.f;
-    }
+  const int tid = threadIdx.x;
+  if constexpr (EPI != EPI_RESID) {
+    wide_rstd(e.ss_in, M, K, e.eps, rs);
     __syncthreads();
   }
   auto sum4 = [&](int m, int n) {  // the S partials of 4 columns, added in split order
@@ -455,9 +461,11 @@ __device__ void wide_reduce(const WideEpi& e, __amdgpu_buffer_rsrc_t pr, int S, 
 // which holds it at 120 VGPRs (four waves per SIMD).  On the 7B shapes at 64
 // rows: gate|up 54.0 -> 50.8 us, QKV 32.7 -> 31.6 us, down 29.3 -> 25.5 us.
 // The reduction fused into the last split (EPI_STORE / _SWIGLU / _RESID)
-// measured 1-2 us faster per projection than GEMM + reduction kernel at 16
-// rows and 1-5 us slower at 64, where the O and down projections' 32 tiles
-// then reduce on 32 CUs; the engine uses it up to 16 rows.
+// measured 1-2 us faster per residual projection than GEMM + reduction kernel at
+// 16 rows and 1-5 us slower at 64, where the O and down projections' 32 tiles
+// then reduce on 32 CUs; the engine uses it up to 16 rows.  For SwiGLU with
+// several splits it was slower at every row count (d = 2048, two splits, 16 rows:
+// 13.4 against 9.9 us with k_part_swiglu).
 template <int MB, int LO, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_wide(const f16* __restrict__ xhi, const f16* __restrict__ xlo,
                                                    const f16* __restrict__ W, int M, int K,
@@ -513,6 +521,10 @@ __global__ __launch_bounds__(512) void k_gemm_wide(const f16* __restrict__ xhi, 
   f32x4 acc[MB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // one split: the SwiGLU epilogue runs from registers (see the end)
+  __shared__ float rs1[EPI == EPI_SWIGLU ? 64 : 1];
+  const bool direct = EPI == EPI_SWIGLU && S == 1;
+  if (direct) wide_rstd(ep.ss_in, M, K, ep.eps, rs1);
 
   // one K chunk t: its MFMAs from stage t & 1 and weights w, then staging chunk
   // t+1, the activation loads of chunk t+2 and the weight loads of chunk t+WP
@@ -594,6 +606,37 @@ __global__ __launch_bounds__(512) void k_gemm_wide(const f16* __restrict__ xhi, 
       if (tok >= M) continue;
       float* dst = part + ((size_t)sp * M + tok) * N + n0 + 4 * g;
       *(float4*)dst = float4{acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]};
+    }
+  } else if (direct) {
+    // even waves hold gate rows, odd waves the up rows of the same 16 outputs: the up
+    // values pass through the staging LDS, and the outputs leave without the partial
+    // sums' trip through memory and without a second launch (7B gate|up, 16 rows: 37.6
+    // us as four splits with their reduction, 33.6 as one split and k_part_swiglu, 32.0
+    // so; 64 rows 52.2, 49.7 and 48.6)
+    f32x4* up = (f32x4*)xs;  // [4 pairs][MB][64 lanes]; the last step's reads of xs are done (its barrier)
+    if (wave & 1) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) up[((wave >> 1) * MB + mb) * 64 + lane] = acc[mb];
+    }
+    __syncthreads();
+    if (wave & 1) return;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const int tok = mb * 16 + r;
+      if (tok >= M) continue;
+      const f32x4 u4 = up[((wave >> 1) * MB + mb) * 64 + lane];
+      const float sc = rs1[tok];
+      const size_t o = (size_t)tok * ep.ldo + (n0 >> 1) + 4 * g;
+      typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+      half4v hi, lo;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float y = silu(acc[mb][e] * sc) * (u4[e] * sc);
+        hi[e] = sat16(y);
+        lo[e] = sat16(y - (float)hi[e]);
+      }
+      *(half4v*)((f16*)ep.out + o) = hi;
+      if (ep.olo) *(half4v*)((f16*)ep.olo + o) = lo;
     }
   } else {
     __shared__ int last;
