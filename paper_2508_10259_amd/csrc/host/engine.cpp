@@ -152,7 +152,7 @@ hipError_t ctx_init(Ctx& c, std::string& err) {
   TRY(hipStreamSynchronize(s));
   c.splits = decode_splits(c.lay.batch, m.n_heads, c.lay.capacity);
   c.meta_host.assign(c.lay.meta_ints, 0);
-  c.fused_grid = fused_applies(c) ? decode_fused_grid(c.model->device, m.head_dim) : 0;
+  c.fused_grid = fused_applies(c) ? decode_fused_grid(c.model->device, m.head_dim, m.d_model) : 0;
   if (c.fused_grid > 0) {
     c.split_o = fused_split(m, m.d_model, c.fused_grid);
     c.split_d = fused_split(m, m.d_ffn, c.fused_grid);

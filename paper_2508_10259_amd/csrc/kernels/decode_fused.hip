@@ -40,6 +40,7 @@ namespace {
 
 typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t Rsrc;
+typedef __attribute__((address_space(3))) void* fused_lds_ptr;
 constexpr int CP_SC1 = 16;  // cache-policy bits of a buffer access: sc1
 
 __device__ __forceinline__ Rsrc rsrc(const void* p, uint32_t bytes) {
@@ -86,6 +87,8 @@ constexpr int SYNC_ERROR = 17 * SYNC_LINE;
 constexpr int SYNC_STRIP = 32 * SYNC_LINE;  // + strip: split-K arrival counters
 constexpr unsigned SPIN_LIMIT = 1u << 22;   // polls (about a second or more) before a wait gives up
 
+constexpr int FUSED_X_CHUNKS = 32;  // inputs of up to 4,096: 128 KB
+
 struct FusedSmem {
   float red[8 * 2 * 256];  // [wave][rb][lane][4] GEMV partial sums
   float wsum[8 * 16];      // [wave][token] RMS statistic partials
@@ -95,6 +98,9 @@ struct FusedSmem {
   int tok[8];              // feed: argmax per row
   int last;                // split-K: this workgroup finishes the strip
   int stop;                // a barrier wait timed out somewhere
+  // activation fragments of a phase whose units all read the same input
+  // ([chunk][step][lane]; every wave stages and reads its own chunks)
+  uint4 x[FUSED_X_CHUNKS * 4 * 64];
 };
 
 // Registers a wave fills for the next phase while it waits at the barrier:
@@ -218,6 +224,33 @@ __device__ __forceinline__ void prefetch_gemv(const f16* W, int K, int n0, int c
   load_w<RB>(W, K, n0, w0 + GB<RB>::CB, w1, *(uint4(*)[8])(pf.a + 8));
 }
 
+// A unit's per-wave sums to sm.red; NRM: 1/rms of each token (the sums of squares
+// over all of K) to sm.rstd.
+template <int RB, bool NRM>
+__device__ __forceinline__ void gemv_reduce(const f32x4 (&acc)[RB], float ss0, float ss1, int K, float eps,
+                                            FusedSmem& sm) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sm.red[((wave * RB + rb) * 64 + lane) * 4 + i] = acc[rb][i];
+  if constexpr (NRM) {
+    float ss = ss0 + ss1;
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    if (lane < 16) sm.wsum[wave * 16 + lane] = ss;
+  }
+  __syncthreads();
+  if constexpr (NRM) {
+    if (threadIdx.x < 16) {
+      float t = 0.f;
+      for (int w = 0; w < 8; ++w) t += sm.wsum[w * 16 + threadIdx.x];
+      sm.rstd[threadIdx.x] = 1.0f / sqrtf(t / (float)K + eps);
+    }
+    __syncthreads();
+  }
+}
+
 // GEMV of one unit: rows n0 .. n0 + 16*RB - 1 of W [N][K] (fp16) over K chunks
 // [c0, c1) of 128 for up to 8 tokens, input the fp16 pair x = hi + lo read
 // through xr (hi at byte 0, lo at lo_off, each [M][K]); the first two
@@ -229,7 +262,7 @@ __device__ __forceinline__ void gemv_unit(const f16* __restrict__ W, int K, int 
                                           uint32_t lo_off, int M, float eps, FusedSmem& sm, Prefetch& pf,
                                           bool use_pf) {
   constexpr int CB = GB<RB>::CB;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
   const int r = lane & 15, g = lane >> 4;
   int w0, w1;
   wave_chunks(c0, c1, w0, w1);
@@ -265,27 +298,63 @@ __device__ __forceinline__ void gemv_unit(const f16* __restrict__ W, int K, int 
       }
     }
   }
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sm.red[((wave * RB + rb) * 64 + lane) * 4 + i] = acc[rb][i];
-  if constexpr (NRM) {
-    float ss = ss0 + ss1;
-    ss += __shfl_xor(ss, 16, 64);
-    ss += __shfl_xor(ss, 32, 64);
-    if (lane < 16) sm.wsum[wave * 16 + lane] = ss;
-  }
-  __syncthreads();
-  if constexpr (NRM) {
-    if (threadIdx.x < 16) {
-      float t = 0.f;
-      for (int w = 0; w < 8; ++w) t += sm.wsum[w * 16 + threadIdx.x];
-      sm.rstd[threadIdx.x] = 1.0f / sqrtf(t / (float)K + eps);
-    }
-    __syncthreads();
-  }
+  gemv_reduce<RB, NRM>(acc, ss0, ss1, K, eps, sm);
 }
 
+// The unit of gemv_unit<RB, true> for inputs of at most FUSED_X_CHUNKS chunks: a
+// wave's share of the activations goes from memory straight to LDS (device-scope
+// loads, all in flight at once) for the workgroup's first unit of the phase and
+// stays there for the others, and the first two batches of the unit at rows nxt
+// (-1: none) are requested before this one's sums meet.  So between a workgroup's
+// units the weight stream does not stop for the activations, the reduction and
+// the first weights (7B, one row, three QKV and three gate|up units per workgroup:
+// 16.16 -> 15.79 ms per step).  W of the first two batches is in pf.
+template <int RB>
+__device__ __forceinline__ void gemv_unit_x(const f16* __restrict__ W, int K, int n0, Rsrc xr, uint32_t lo_off, int M,
+                                            float eps, FusedSmem& sm, Prefetch& pf, bool first, int nxt) {
+  constexpr int CB = GB<RB>::CB;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  int w0, w1;
+  wave_chunks(0, K >> 7, w0, w1);
+  f32x4 acc[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float ss0 = 0.f, ss1 = 0.f;
+  uint4(&wa)[8] = *(uint4(*)[8])pf.a;
+  uint4(&wb)[8] = *(uint4(*)[8])(pf.a + 8);
+  if (first) {
+    const int tk = r & 7;  // as in gemv_unit
+    const uint32_t xo = (r >= 8 ? lo_off : 0u) + (uint32_t)(((tk < M ? tk : 0) * K + g * 8) * 2);
+    for (int c = w0; c < w1; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (fused_lds_ptr)(sm.x + (c * 4 + i) * 64), 16,
+                                                 (int)(xo + ((uint32_t)c * 128u + 32u * i) * 2u), 0, 0, CP_SC1);
+    vm_drain();  // this wave's own chunks: no barrier
+  }
+  auto batch = [&](const uint4(&w)[8], int cb) __attribute__((always_inline)) {
+    uint4 x[8];
+#pragma unroll
+    for (int j = 0; j < CB; ++j)
+      if (cb + j < w1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[j * 4 + i] = sm.x[((cb + j) * 4 + i) * 64 + lane];
+    mma_batch<RB, true>(w, x, cb, w1, acc, ss0, ss1);
+  };
+  for (int cb = w0; cb < w1; cb += 2 * CB) {
+    batch(wa, cb);
+    if (cb + 2 * CB < w1) load_w<RB>(W, K, n0, cb + 2 * CB, w1, wa);
+    if (cb + CB < w1) {
+      batch(wb, cb + CB);
+      if (cb + 3 * CB < w1) load_w<RB>(W, K, n0, cb + 3 * CB, w1, wb);
+    }
+  }
+  if (nxt >= 0) {
+    load_w<RB>(W, K, nxt, w0, w1, wa);
+    load_w<RB>(W, K, nxt, w0 + CB, w1, wb);
+  }
+  gemv_reduce<RB, true>(acc, ss0, ss1, K, eps, sm);
+}
 // Sum over the waves and over the hi / lo columns of value (rb, ln, i): packed
 // row n0 + rb*16 + 4*(ln >> 4) + i, token ln & 15 (< 8).
 template <int RB>
@@ -338,11 +407,16 @@ __device__ __forceinline__ const f16* layer_w(const f16* base, size_t stride, in
 
 // y = W x * rstd (x the pair read through xr), stored fp32 at out[tok*ldo + n]
 // (sc1); j_head >= 0 (the head) also writes the caller's out_logits for bins < n_bins.
+template <bool XL>
 __device__ void phase_store(const FusedArgs& a, const f16* W, int N, int K, Rsrc xr, uint32_t lo_off, Rsrc outr,
                             int ldo, int j_head, FusedSmem& sm, Prefetch& pf) {
-  const int units = N / 16;
-  for (int u = blockIdx.x; u < units; u += gridDim.x) {
-    gemv_unit<1, true>(W, K, u * 16, 0, K >> 7, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x);
+  const int units = N / 16, G = gridDim.x;
+  for (int u = blockIdx.x; u < units; u += G) {
+    if constexpr (XL)
+      gemv_unit_x<1>(W, K, u * 16, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x,
+                     u + G < units ? (u + G) * 16 : -1);
+    else
+      gemv_unit<1, true>(W, K, u * 16, 0, K >> 7, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x);
     if (threadIdx.x < 256) {
       const int ln = threadIdx.x >> 2, i = threadIdx.x & 3, tok = ln & 15;
       if (tok < 8 && tok < a.M) {
@@ -361,13 +435,19 @@ __device__ __forceinline__ void prefetch_store(const f16* W, int N, int K, Prefe
 }
 
 // a = silu(gate) * up of the packed gate|up rows (32-row units), as an fp16 pair.
+template <bool XL>
 __device__ void phase_swiglu(const FusedArgs& a, const f16* W, Rsrc xr, uint32_t lo_off, FusedSmem& sm,
                              Prefetch& pf) {
   const int F = a.F, units = (2 * F) / 32;
   const Rsrc apr = rsrc(a.ap, (uint32_t)(2 * a.M * F * 2));
   const uint32_t alo = (uint32_t)(a.M * F * 2);
-  for (int u = blockIdx.x; u < units; u += gridDim.x) {
-    gemv_unit<2, true>(W, a.d, u * 32, 0, a.d >> 7, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x);
+  const int G = gridDim.x;
+  for (int u = blockIdx.x; u < units; u += G) {
+    if constexpr (XL)
+      gemv_unit_x<2>(W, a.d, u * 32, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x,
+                     u + G < units ? (u + G) * 32 : -1);
+    else
+      gemv_unit<2, true>(W, a.d, u * 32, 0, a.d >> 7, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x);
     if (threadIdx.x < 256) {
       const int ln = threadIdx.x >> 2, i = threadIdx.x & 3, tok = ln & 15;
       if (tok < 8 && tok < a.M) {
@@ -757,7 +837,8 @@ __device__ void phase_feed(const FusedArgs& a, int j, bool feed, FusedSmem& sm) 
   }
 }
 
-template <int DH>
+// XL: d is at most 128 FUSED_X_CHUNKS, the phases that read h keep it in LDS
+template <int DH, bool XL>
 __global__ __launch_bounds__(512) void k_decode_fused(FusedArgs a) {
   __shared__ FusedSmem sm;
   if (threadIdx.x == 0) sm.stop = 0;
@@ -780,7 +861,7 @@ __global__ __launch_bounds__(512) void k_decode_fused(FusedArgs a) {
   } while (0)
 
   prefetch_store(a.whead, a.nbp, d, pf);
-  phase_store(a, a.whead, a.nbp, d, hlr, a.hl_lo, logr, a.nbp, 0, sm, pf);
+  phase_store<XL>(a, a.whead, a.nbp, d, hlr, a.hl_lo, logr, a.nbp, 0, sm, pf);
   for (int j = 1; j < a.A; ++j) {
     AMS_SYNC((void)0);
     phase_feed(a, j - 1, true, sm);
@@ -790,19 +871,19 @@ __global__ __launch_bounds__(512) void k_decode_fused(FusedArgs a) {
       const f16* wo = layer_w(a.wo, a.s_o, l);
       const f16* wgu = layer_w(a.wgu, a.s_gu, l);
       const f16* wd = layer_w(a.wd, a.s_d, l);
-      phase_store(a, wqkv, 3 * d, d, hpr, hlo, qkvr, 3 * d, -1, sm, pf);
+      phase_store<XL>(a, wqkv, 3 * d, d, hpr, hlo, qkvr, 3 * d, -1, sm, pf);
       AMS_SYNC(prefetch_attn<DH>(a, l, j - 1, pf));
       phase_attn<DH>(a, l, j - 1, sm, pf);
       AMS_SYNC(prefetch_resid(a, wo, d, a.split_o, pf));
       phase_resid(a, wo, d, a.split_o, opr, olo, sm, pf);
       AMS_SYNC(prefetch_swiglu(a, wgu, pf));
-      phase_swiglu(a, wgu, hpr, hlo, sm, pf);
+      phase_swiglu<XL>(a, wgu, hpr, hlo, sm, pf);
       AMS_SYNC(prefetch_resid(a, wd, a.F, a.split_d, pf));
       phase_resid(a, wd, a.F, a.split_d, apr, alo, sm, pf);
       if (l + 1 < a.L) AMS_SYNC(prefetch_store(layer_w(a.wqkv, a.s_qkv, l + 1), 3 * d, d, pf));
       else AMS_SYNC(prefetch_store(a.whead, a.nbp, d, pf));
     }
-    phase_store(a, a.whead, a.nbp, d, hpr, hlo, logr, a.nbp, j, sm, pf);
+    phase_store<XL>(a, a.whead, a.nbp, d, hpr, hlo, logr, a.nbp, j, sm, pf);
   }
   AMS_SYNC((void)0);
 #undef AMS_SYNC
@@ -822,14 +903,19 @@ __global__ void k_fused_reset(unsigned* sync, int words) {
 
 int fused_sync_words(int d, int H) { return SYNC_STRIP + (d / 16 > 8 * H ? d / 16 : 8 * H); }
 
+typedef void (*FusedKernel)(FusedArgs);
+static FusedKernel fused_kernel(int dh, int d) {
+  const bool xl = d / 128 <= FUSED_X_CHUNKS;
+  if (dh == 64) return xl ? k_decode_fused<64, true> : k_decode_fused<64, false>;
+  return xl ? k_decode_fused<128, true> : k_decode_fused<128, false>;
+}
+
 // Largest grid that is resident at once: one workgroup per compute unit when
 // the kernel fits (0 if not).
-int decode_fused_grid(int device, int dh) {
+int decode_fused_grid(int device, int dh, int d) {
   int cus = 0, per_cu = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return 0;
-  const hipError_t e = dh == 64
-                           ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_decode_fused<64>, 512, 0)
-                           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_decode_fused<128>, 512, 0);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fused_kernel(dh, d), 512, 0);
   if (e != hipSuccess || per_cu < 1) return 0;
   return cus;
 }
@@ -859,8 +945,7 @@ hipError_t decode_fused(const FusedDecode& f, int grid, hipStream_t s) {
   hipLaunchKernelGGL(k_fused_reset, dim3((words + 255) / 256), dim3(256), 0, s, f.sync, words);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (f.dh == 64) hipLaunchKernelGGL(k_decode_fused<64>, dim3(grid), dim3(512), 0, s, a);
-  else hipLaunchKernelGGL(k_decode_fused<128>, dim3(grid), dim3(512), 0, s, a);
+  hipLaunchKernelGGL(fused_kernel(f.dh, f.d), dim3(grid), dim3(512), 0, s, a);
   return hipGetLastError();
 }
 

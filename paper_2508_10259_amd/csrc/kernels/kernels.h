@@ -280,7 +280,7 @@ struct FusedDecode {
 hipError_t decode_fused(const FusedDecode& f, int grid, hipStream_t s);
 // Workgroups of the persistent decode on `device` (one per compute unit), 0 if
 // it cannot be resident there.
-int decode_fused_grid(int device, int dh);
+int decode_fused_grid(int device, int dh, int d);
 int fused_sync_words(int d, int H);
 
 // lens[b] += add[b] (device arrays), or, when `set`, lens[b] = add[b] for the

@@ -36,3 +36,25 @@ def test_short_passes(F, lens, news):
             c = compare(zr, z[b], tok[b], TOL_BF16)
             log(f"F={F} lens={lens} step {s} row {b}: max abs {c.max_abs:.2e}")
             assert c.max_abs <= TOL_BF16 and c.band == 1.0
+
+
+@pytest.mark.parametrize("d,H,F", [(4096, 32, 4224), (4224, 33, 256)])
+def test_persistent_decode_widths(d, H, F):
+    """The persistent decode on both sides of the width up to which it keeps a phase's activations
+    in LDS, with one to three units of a phase per workgroup."""
+    from paper_2508_10259_amd.runtime import DeviceContext
+    spec = small_spec("bf16", 1, d, H, F)
+    pair = Pair(spec, seed=33)
+    B, A, lens = 3, 4, (9, 70, 33)
+    pre = [_prefix(spec, 33, 0, b, n) for b, n in enumerate(lens)]
+    prefix, plens = pair.dev.pack_prefixes(pre)
+    ctx = DeviceContext(pair.dev, B, 128)
+    assert ctx.persistent_decode
+    refs = [ForcedRef(pair.p, x) for x in pair.prefixes_f64(pre)]
+    ctx.build(prefix, plens)
+    tok, z = ctx.step(A)
+    tok, z = tok.cpu().numpy(), z.cpu().numpy()
+    for b in range(B):
+        c = compare(refs[b].step(None, tok[b]), z[b], tok[b], TOL_BF16)
+        log(f"d={d} row {b}: max abs {c.max_abs:.2e}")
+        assert c.max_abs <= TOL_BF16 and c.band == 1.0
