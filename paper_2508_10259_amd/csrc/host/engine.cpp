@@ -56,7 +56,7 @@ static bool wide_decode(const Ctx& c, int rows, int N) {
 }
 
 // On the wide path the RMSNorm of a projection input needs no kernel of its
-// own once a residual reduction has run: it leaves the unnormalised fp16 pair
+// own once a residual reduction or the feed has run: it leaves the unnormalised fp16 pair
 // of h in (u, hlo) and its sums of squares per 128 columns, and the
 // projection's reduction divides its rows by rms.
 // Up to 16 rows the wide GEMM reduces its split-K partial sums in each tile's
@@ -320,7 +320,7 @@ static hipError_t tokens_resid(Ctx& c, const void* x, const void* W, const void*
   normed = false;
   if (short_f32(md, M)) return resid_f32(c, x, W, M, K, c.h(), s);
   if (short_wide(md, M, d, K, true)) {
-    const int S = decode_wsplit(d, K);
+    const int S = decode_wsplit(d, K, M);
     if (wide_fused_reduce(M))
       return gemm_wide_reduce(EPI_RESID, x, nullptr, Wf, M, d, K, S, c.kpart(), c.wcnt(), nullptr, nullptr, 0, c.h(),
                               nullptr, nullptr, nullptr, nullptr, 0.f, s);
@@ -343,7 +343,7 @@ static hipError_t tokens_resid(Ctx& c, const void* x, const void* W, const void*
 // A projection of u on the wide GEMM (short_wide).
 static hipError_t short_proj(const Ctx& c, int epi, const void* Wf, int M, int N, int K, void* out, int ldo,
                              hipStream_t s) {
-  const int S = decode_wsplit(N, K);
+  const int S = decode_wsplit(N, K, M);
   if (epi == EPI_SWIGLU ? S == 1 : wide_fused_reduce(M))
     return gemm_wide_reduce(epi, c.u(), nullptr, Wf, M, N, K, S, c.kpart(), c.wcnt(), out, nullptr, ldo, nullptr,
                             nullptr, nullptr, nullptr, nullptr, 0.f, s);
@@ -541,7 +541,7 @@ static hipError_t norm_proj(const Rows& g, int epi, const float* h, const void* 
       TRY(rmsnorm(md.ct, h, g.n, K, eps, g.u(), s, ulo));
     }
     if (wide) {  // partial sums of 128-row tiles, then the epilogue
-      const int splits = decode_wsplit(N, K);
+      const int splits = decode_wsplit(N, K, g.n);
       if (epi == EPI_SWIGLU ? splits == 1 : !defer && wide_fused_reduce(g.n)) {
         TRY(gemm_wide_reduce(epi, g.u(), ulo, Wf, g.n, N, K, splits, g.c->kpart(), g.c->wcnt(), out, olo, ldo, nullptr,
                              nullptr, nullptr, nullptr, ss, eps, s));
@@ -573,7 +573,7 @@ static hipError_t resid_proj(const Rows& g, const void* x, const void* xlo, cons
   const Model& md = *c.model;
   const int d = md.cfg.d_model;
   if (wide_decode(c, g.n, d)) {
-    const int splits = decode_wsplit(d, K);
+    const int splits = decode_wsplit(d, K, g.n);
     void* o16 = ss ? g.u() : hhi;
     void* olo = ss ? g.hlo() : hlo;
     if (wide_fused_reduce(g.n))
@@ -604,12 +604,12 @@ static hipError_t layer_decode(const Rows& g, int l, int jpos, hipStream_t s, st
   void* hlo = fused ? g.hlo() : nullptr;
   void* olo = f16 ? g.olo() : nullptr;   // lo parts of the attention and SwiGLU outputs
   void* alo = f16 ? g.alo() : nullptr;
-  // sums of squares of h from the previous residual reduction (from layer 1 on)
+  // sums of squares of h from the feed or the previous residual reduction
   float* ss = merge_norm(c, B) ? g.ss() : nullptr;
   // on the wide path the attention adds the QKV projection's partial sums itself
   QkvParts qp{};
   if (norm_proj(g, EPI_STORE, g.h(), hhi, hlo, md.wqkv(l), md.fqkv(l), 3 * d, d, g.qkv(), 3 * d, nullptr, s, err,
-                l > 0 ? ss : nullptr, &qp) != hipSuccess)
+                ss, &qp) != hipSuccess)
     return hipErrorLaunchFailure;
   TRY(attn_decode(dt, g.qkv(), g.lens(), jpos, B, m.n_heads, m.head_dim, c.lay.capacity, g.pages(), c.splits, c.rope(),
                   g.kslab(l), g.vslab(l), g.part(), g.o(), s, olo, qp, B > 1 ? g.order() : nullptr));
@@ -630,12 +630,13 @@ static hipError_t head(const Rows& g, const float* hin, const void* hhi, const v
   const Model& md = *g.c->model;
   const Cfg& m = md.cfg;
   const int d = m.d_model, nbp = bins_padded(m);
-  const bool fused = fused_norm(*g.c, g.n);
+  const bool fused = fused_norm(*g.c, g.n), merged = merge_norm(*g.c, g.n);
   if (norm_proj(g, EPI_STORE, hin, hhi, hlo, md.head_bins(), md.fhead(), nbp, d, g.logits(), nbp, nullptr, s, err, ss) !=
       hipSuccess)
     return hipErrorLaunchFailure;
   TRY(argmax_feed(md.ct, g.logits(), nbp, md.bin_embed(), g.n, d, m.n_bins, A, j, tok, logits, forced, g.h(),
-                  j + 1 < A, s, fused ? g.u() : nullptr, fused ? g.hlo() : nullptr));
+                  j + 1 < A, s, fused || merged ? g.u() : nullptr, fused || merged ? g.hlo() : nullptr,
+                  merged && j + 1 < A ? g.ss() : nullptr));
   return hipSuccess;
 }
 

@@ -144,17 +144,19 @@ inline int decode_ksplit(int N, int K) {
   return std::max(1, s);
 }
 
-// K splits of a wide GEMM (128 weight rows per workgroup; at least 2 chunks of
-// 128 per split, at most 8 splits): about 192 workgroups.  That many stream the
-// weights as fast as 256 or 384 do, and every further split adds partial sums.
+// K splits of a wide GEMM over M rows (128 weight rows per workgroup; at least 2
+// chunks of 128 per split, at most 8 splits, 16 for the few tiles of an action
+// head): about 192 workgroups.  That many stream the weights as fast as 256 or 384
+// do, and every further split adds partial sums.  Above 16 rows, where a
+// separate launch adds them whatever their number, few tiles take 256 workgroups.
 // Measured with 9 to 64 rows against the former rule (the smallest of 16 within 5%
 // of the best ratio of work to rounds of 256), us per projection with its reduction:
-// 7B gate|up 4 -> 1 splits 36 -> 31 at 9 rows, 52 -> 49 at 64; O 8 -> 6 12.0 ->
-// 11.2 and 19.9 -> 17.6; down 8 -> 6 18.7 -> 18.8 and 32.2 -> 29.1; d = 2048 QKV 2 -> 4
-// 8.7 -> 7.5 and 13.5 -> 10.3; d = 1024 O 2 -> 4 8.0 -> 6.5 and 11.0 -> 9.9.
-inline int decode_wsplit(int N, int K) {
-  const int tiles = std::max(N / 128, 1);
-  return std::max(1, std::min({(2 * 192 + tiles) / (2 * tiles), (K / 128) / 2, 8}));
+// 7B gate|up 4 -> 1 splits 36 -> 31 at 9 rows, 51.1 -> 50.3 at 64; O 8 -> 6 12.0 ->
+// 11.2 at 9 rows (at 64 rows O and down average 18.3 with 8, 19.6 with 6); d = 2048
+// QKV 2 -> 4 8.7 -> 7.5 and 13.5 -> 10.3; d = 1024 O 2 -> 4 8.0 -> 6.5 and 11.0 -> 9.9.
+inline int decode_wsplit(int N, int K, int M) {
+  const int tiles = std::max(N / 128, 1), wgs = M > 16 && tiles <= 32 ? 256 : 192;
+  return std::max(1, std::min({(2 * wgs + tiles) / (2 * tiles), (K / 128) / 2, tiles < 8 ? 16 : 8}));
 }
 
 // Persistent decode (one launch per step) applies up to this many rows.
@@ -252,14 +254,14 @@ inline CtxLayout ctx_layout(const Cfg& c, int batch, int capacity, int pass_toke
   if (ks > 1) kp = ks * B * d;
   if (batch > 8 && batch <= 64) {
     const size_t NB = bins_padded(c);
-    kp = std::max({kp, decode_wsplit(3 * (int)d, (int)d) * B * 3 * d, decode_wsplit((int)d, (int)d) * B * d,
-                   decode_wsplit(2 * (int)F, (int)d) * B * 2 * F, decode_wsplit((int)d, (int)F) * B * d,
-                   decode_wsplit((int)NB, (int)d) * B * NB});
+    kp = std::max({kp, decode_wsplit(3 * (int)d, (int)d, 64) * B * 3 * d, decode_wsplit((int)d, (int)d, 64) * B * d,
+                   decode_wsplit(2 * (int)F, (int)d, 64) * B * 2 * F, decode_wsplit((int)d, (int)F, 64) * B * d,
+                   decode_wsplit((int)NB, (int)d, 64) * B * NB});
   }
   if (es == 2) {  // token passes of up to 64 tokens, and longer ones
     const size_t m = std::min<size_t>(T, 64);
-    kp = std::max({kp, decode_wsplit(3 * (int)d, (int)d) * m * 3 * d, decode_wsplit((int)d, (int)d) * m * d,
-                   decode_wsplit(2 * (int)F, (int)d) * m * 2 * F, decode_wsplit((int)d, (int)F) * m * d});
+    kp = std::max({kp, decode_wsplit(3 * (int)d, (int)d, 64) * m * 3 * d, decode_wsplit((int)d, (int)d, 64) * m * d,
+                   decode_wsplit(2 * (int)F, (int)d, 64) * m * 2 * F, decode_wsplit((int)d, (int)F, 64) * m * d});
     kp = std::max({kp, tok_part_floats((int)d, (int)d, x.pass_tokens), tok_part_floats((int)d, (int)F, x.pass_tokens)});
   } else kp = std::max(kp, (size_t)std::max(f32_split((int)d, (int)d), f32_split((int)d, (int)F)) * std::min<size_t>(T, 64) * d);
   x.kpart = o; o = align256(o + kp * 4);

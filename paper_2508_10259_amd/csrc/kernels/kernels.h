@@ -145,10 +145,11 @@ hipError_t gemv_rmsnorm(int ct, int epi, const void* hhi, float eps, const void*
 // logits copied to out_logits[b][j] (if non-NULL); when feed, h[b] = bin_embed[t]
 // with t the argmax or the clamped forced[b*A+j], and (if h16 is non-NULL, fp16
 // compute only) h16[b] = the same row in fp16 and h16lo[b] (if non-NULL) = 0,
-// its rounding error.
+// its rounding error; with ss (fp16 compute, when feeding) also the sums of squares
+// of h[b] per 128 columns, ss[b][d / 128].  d is a multiple of 128 when feeding.
 hipError_t argmax_feed(int ct, const float* logits, int ld_logits, const void* bin_embed, int B, int d, int n_bins,
                        int A, int j, int32_t* out_tok, float* out_logits, const int32_t* forced, float* h, int feed,
-                       hipStream_t s, void* h16 = nullptr, void* h16lo = nullptr);
+                       hipStream_t s, void* h16 = nullptr, void* h16lo = nullptr, float* ss = nullptr);
 
 // u[m] = h[m] / sqrt(mean(h[m]^2) + eps), written in the compute type (the
 // gain is folded into the weights that consume u).

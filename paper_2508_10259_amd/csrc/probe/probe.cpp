@@ -133,6 +133,12 @@ int ams_probe_rmsnorm(int dtype, const float* h, int M, int d, float eps, void* 
   return (int)ams::rmsnorm(dtype, h, M, d, eps, u, (hipStream_t)stream, ulo);
 }
 
+// feeding with the sums of squares of the fed rows per 128 columns
+int ams_probe_argmax_feed_ss(const float* logits, int ld, const void* bin_embed, int B, int d, int n_bins,
+                             int32_t* out_tok, float* h, void* h16, void* h16lo, float* ss, void* stream) {
+  return (int)ams::argmax_feed(ams::DT_F16, logits, ld, bin_embed, B, d, n_bins, 1, 0, out_tok, nullptr, nullptr, h, 1,
+                               (hipStream_t)stream, h16, h16lo, ss);
+}
 int ams_probe_argmax_feed(int ct, const float* logits, int ld, const void* bin_embed, int B, int d, int n_bins,
                           int A, int j, int32_t* out_tok, float* out_logits, const int32_t* forced, float* h, int feed,
                           void* h16, void* h16lo, void* stream) {
