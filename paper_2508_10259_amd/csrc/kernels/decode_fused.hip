@@ -92,7 +92,6 @@ constexpr int FUSED_X_CHUNKS = 32;  // inputs of up to 4,096: 128 KB
 struct FusedSmem {
   float red[8 * 2 * 256];  // [wave][rb][lane][4] GEMV partial sums
   float wsum[8 * 16];      // [wave][token] RMS statistic partials
-  float rstd[16];
   float am[8], al[8];      // attention: per-wave max and sum
   float aacc[8][128];      // attention: per-wave output
   int tok[8];              // feed: argmax per row
@@ -224,11 +223,10 @@ __device__ __forceinline__ void prefetch_gemv(const f16* W, int K, int n0, int c
   load_w<RB>(W, K, n0, w0 + GB<RB>::CB, w1, *(uint4(*)[8])(pf.a + 8));
 }
 
-// A unit's per-wave sums to sm.red; NRM: 1/rms of each token (the sums of squares
-// over all of K) to sm.rstd.
+// A unit's per-wave sums to sm.red; NRM: each wave's sums of squares per token to
+// sm.wsum.
 template <int RB, bool NRM>
-__device__ __forceinline__ void gemv_reduce(const f32x4 (&acc)[RB], float ss0, float ss1, int K, float eps,
-                                            FusedSmem& sm) {
+__device__ __forceinline__ void gemv_reduce(const f32x4 (&acc)[RB], float ss0, float ss1, FusedSmem& sm) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
@@ -241,26 +239,28 @@ __device__ __forceinline__ void gemv_reduce(const f32x4 (&acc)[RB], float ss0, f
     if (lane < 16) sm.wsum[wave * 16 + lane] = ss;
   }
   __syncthreads();
-  if constexpr (NRM) {
-    if (threadIdx.x < 16) {
-      float t = 0.f;
-      for (int w = 0; w < 8; ++w) t += sm.wsum[w * 16 + threadIdx.x];
-      sm.rstd[threadIdx.x] = 1.0f / sqrtf(t / (float)K + eps);
-    }
-    __syncthreads();
-  }
+}
+
+// 1/rms of token tok over all of K, from the waves' sums of squares: in every
+// thread that stores, while its own sums come from LDS.  One thread per token and
+// a second workgroup barrier lay in each unit's chain before (12-layer d = 1024
+// decoder, 8 rows: 2,042 -> 2,028 us per step).
+__device__ __forceinline__ float gemv_rstd(const FusedSmem& sm, int tok, int K, float eps) {
+  float t = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) t += sm.wsum[w * 16 + tok];
+  return 1.0f / sqrtf(t / (float)K + eps);
 }
 
 // GEMV of one unit: rows n0 .. n0 + 16*RB - 1 of W [N][K] (fp16) over K chunks
 // [c0, c1) of 128 for up to 8 tokens, input the fp16 pair x = hi + lo read
 // through xr (hi at byte 0, lo at lo_off, each [M][K]); the first two
 // batches' weights come from pf when use_pf.  The sums over the waves are left in
-// sm.red; NRM also leaves 1/rms of each token (statistic of hi over all of K,
-// which the unit must then cover) in sm.rstd.
+// sm.red; NRM also leaves each token's sums of squares (of hi, over the K that the
+// unit covers: all of it for gemv_rstd) in sm.wsum.
 template <int RB, bool NRM>
 __device__ __forceinline__ void gemv_unit(const f16* __restrict__ W, int K, int n0, int c0, int c1, Rsrc xr,
-                                          uint32_t lo_off, int M, float eps, FusedSmem& sm, Prefetch& pf,
-                                          bool use_pf) {
+                                          uint32_t lo_off, int M, FusedSmem& sm, Prefetch& pf, bool use_pf) {
   constexpr int CB = GB<RB>::CB;
   const int lane = threadIdx.x & 63;
   const int r = lane & 15, g = lane >> 4;
@@ -298,7 +298,7 @@ __device__ __forceinline__ void gemv_unit(const f16* __restrict__ W, int K, int 
       }
     }
   }
-  gemv_reduce<RB, NRM>(acc, ss0, ss1, K, eps, sm);
+  gemv_reduce<RB, NRM>(acc, ss0, ss1, sm);
 }
 
 // The unit of gemv_unit<RB, true> for inputs of at most FUSED_X_CHUNKS chunks: a
@@ -311,7 +311,7 @@ __device__ __forceinline__ void gemv_unit(const f16* __restrict__ W, int K, int 
 // 16.16 -> 15.79 ms per step).  W of the first two batches is in pf.
 template <int RB>
 __device__ __forceinline__ void gemv_unit_x(const f16* __restrict__ W, int K, int n0, Rsrc xr, uint32_t lo_off, int M,
-                                            float eps, FusedSmem& sm, Prefetch& pf, bool first, int nxt) {
+                                            FusedSmem& sm, Prefetch& pf, bool first, int nxt) {
   constexpr int CB = GB<RB>::CB;
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   int w0, w1;
@@ -353,7 +353,7 @@ __device__ __forceinline__ void gemv_unit_x(const f16* __restrict__ W, int K, in
     load_w<RB>(W, K, nxt, w0, w1, wa);
     load_w<RB>(W, K, nxt, w0 + CB, w1, wb);
   }
-  gemv_reduce<RB, true>(acc, ss0, ss1, K, eps, sm);
+  gemv_reduce<RB, true>(acc, ss0, ss1, sm);
 }
 // Sum over the waves and over the hi / lo columns of value (rb, ln, i): packed
 // row n0 + rb*16 + 4*(ln >> 4) + i, token ln & 15 (< 8).
@@ -413,15 +413,15 @@ __device__ void phase_store(const FusedArgs& a, const f16* W, int N, int K, Rsrc
   const int units = N / 16, G = gridDim.x;
   for (int u = blockIdx.x; u < units; u += G) {
     if constexpr (XL)
-      gemv_unit_x<1>(W, K, u * 16, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x,
+      gemv_unit_x<1>(W, K, u * 16, xr, lo_off, a.M, sm, pf, u == (int)blockIdx.x,
                      u + G < units ? (u + G) * 16 : -1);
     else
-      gemv_unit<1, true>(W, K, u * 16, 0, K >> 7, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x);
+      gemv_unit<1, true>(W, K, u * 16, 0, K >> 7, xr, lo_off, a.M, sm, pf, u == (int)blockIdx.x);
     if (threadIdx.x < 256) {
       const int ln = threadIdx.x >> 2, i = threadIdx.x & 3, tok = ln & 15;
       if (tok < 8 && tok < a.M) {
         const int n = u * 16 + 4 * (ln >> 4) + i;
-        const float y = gemv_value<1>(sm, 0, ln, i) * sm.rstd[tok];
+        const float y = gemv_value<1>(sm, 0, ln, i) * gemv_rstd(sm, tok, K, a.eps);
         stcf(outr, (uint32_t)(tok * ldo + n) * 4u, y);
         if (j_head >= 0 && a.out_logits && n < a.n_bins)
           a.out_logits[((size_t)tok * a.A + j_head) * a.n_bins + n] = y;
@@ -444,14 +444,14 @@ __device__ void phase_swiglu(const FusedArgs& a, const f16* W, Rsrc xr, uint32_t
   const int G = gridDim.x;
   for (int u = blockIdx.x; u < units; u += G) {
     if constexpr (XL)
-      gemv_unit_x<2>(W, a.d, u * 32, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x,
+      gemv_unit_x<2>(W, a.d, u * 32, xr, lo_off, a.M, sm, pf, u == (int)blockIdx.x,
                      u + G < units ? (u + G) * 32 : -1);
     else
-      gemv_unit<2, true>(W, a.d, u * 32, 0, a.d >> 7, xr, lo_off, a.M, a.eps, sm, pf, u == (int)blockIdx.x);
+      gemv_unit<2, true>(W, a.d, u * 32, 0, a.d >> 7, xr, lo_off, a.M, sm, pf, u == (int)blockIdx.x);
     if (threadIdx.x < 256) {
       const int ln = threadIdx.x >> 2, i = threadIdx.x & 3, tok = ln & 15;
       if (tok < 8 && tok < a.M) {
-        const float sc = sm.rstd[tok];
+        const float sc = gemv_rstd(sm, tok, a.d, a.eps);
         const float gt = gemv_value<2>(sm, 0, ln, i) * sc, up = gemv_value<2>(sm, 1, ln, i) * sc;
         const float v = silu(gt) * up;
         const f16 hi = sat16(v), lo = sat16(v - (float)hi);
@@ -483,7 +483,7 @@ __device__ void phase_resid(const FusedArgs& a, const f16* W, int K, int S, Rsrc
     // this thread's residual value, written two phases ago: its load overlaps the GEMV
     const uint32_t e = (uint32_t)(tok * d + strip * 16 + row);
     const float h_old = ok ? ldcf(hr, e * 4u) : 0.f;
-    gemv_unit<1, false>(W, K, strip * 16, sp * nch / S, (sp + 1) * nch / S, xr, lo_off, a.M, 0.f, sm, pf,
+    gemv_unit<1, false>(W, K, strip * 16, sp * nch / S, (sp + 1) * nch / S, xr, lo_off, a.M, sm, pf,
                         u == (int)blockIdx.x);
     float y = ok ? gemv_value<1>(sm, 0, ln, i) : 0.f;
     bool fin = true;
