@@ -230,7 +230,7 @@ __global__ __launch_bounds__(512) void k_tok_pp(const f16* __restrict__ u, const
 }
 
 // ----------------------------------------------------------------------------
-// BM tokens x BN weight rows, WM x WN waves, K steps of 64 through NST LDS stages
+// BM tokens x BN weight rows, WM x WN x WK waves, K steps of 64 through NST LDS stages
 // with one barrier per step: a wave waits for its own loads of the step (issued
 // NST - 1 steps earlier), the barrier makes every wave's visible and says that the
 // stage of the step before is read out, and the loads NST - 1 steps ahead go into
@@ -238,17 +238,24 @@ __global__ __launch_bounds__(512) void k_tok_pp(const f16* __restrict__ u, const
 // whole memory round trip, 1.2 us, whatever its size.  Measured on the 7B
 // shapes: 128 tokens QKV 82 -> 34 us, gate|up 82 -> 45 us; 288 tokens QKV 73 -> 49;
 // 600 tokens QKV 89 -> 68 us, gate|up 180 -> 130 us, O 45 -> 30, down 100 -> 65.
-template <int EPI, int BM, int BN, int WM, int WN, int NST>
-__global__ __launch_bounds__(64 * WM * WN) void k_tok_pipe(const f16* __restrict__ u, const f16* __restrict__ W, int M,
+// WK = 2: two waves share a wave tile, each with one of a K step's two MFMA steps, and
+// trade halves of their sums at the end.  Twice the waves on the same LDS traffic: one
+// 128 x 64 workgroup on a CU kept four waves, one per SIMD, that all waited for the
+// same stage (three of them; eight waves and six stages: QKV 34.0 -> 31.5 us at 128 tokens
+// of the 7B width, 30.9 -> 26.5 at 72; 288 tokens of d = 1024 10.0 -> 9.1), and two
+// 128 x 128 workgroups of four gain 1-2% (QKV 288 tokens 59.9 -> 58.5, d = 1024 and 2,240
+// tokens 21.8 -> 21.3).  The tiles whose one workgroup has eight waves anyway do not.
+template <int EPI, int BM, int BN, int WM, int WN, int WK, int NST>
+__global__ __launch_bounds__(64 * WM * WN * WK) void k_tok_pipe(const f16* __restrict__ u, const f16* __restrict__ W, int M,
                                                            int N, int K, void* __restrict__ out, int ldo) {
-  constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, NI = TM / 16, NJ = TN / 16;
+  constexpr int NW = WM * WN * WK, TM = BM / WM, TN = BN / WN, NI = TM / 16, NJ = TN / 16;
   constexpr int AB = BM / 8, BB = BN / 8, LPW = (AB + BB) / NW;  // 1 KB blocks of a stage, loads per wave
   constexpr int STAGE = (AB + BB) * 1024;
   static_assert((AB + BB) % NW == 0, "every wave issues as many loads per stage");
   static_assert(EPI != EPI_SWIGLU || NJ % 2 == 0, "gate and up strips come in pairs");
   extern __shared__ __attribute__((aligned(16))) unsigned char tsm[];  // [stage][AB token | BB weight blocks]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 15, g = lane >> 4, wm = wave / WN, wn = wave % WN;
+  const int r = lane & 15, g = lane >> 4, wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
   int m0, n0;
   tok_tile<BM, BN>(M, N, m0, n0);
   const int alast = M - 1 - m0;
@@ -296,21 +303,47 @@ __global__ __launch_bounds__(64 * WM * WN) void k_tok_pipe(const f16* __restrict
     const unsigned char* cur = tsm + (t % NST) * STAGE;
     const unsigned char* Tb = cur + (wm * TM + r) * 128;
     const unsigned char* Wb = cur + AB * 1024 + wn * NJ * 2048 + lane * 16;
-    half8 tf[2][NI], wf[2][NJ];
+    constexpr int KS = 2 / WK;  // MFMA steps of 32 that this wave takes of the K step
+    half8 tf[KS][NI], wf[KS][NJ];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
+    for (int k = 0; k < KS; ++k) {
+      const int ks = WK == 2 ? wk : k;
 #pragma unroll
-      for (int i = 0; i < NI; ++i) tf[ks][i] = *(const half8*)(Tb + i * 2048 + (((4 * ks + g) ^ (r & 7)) << 4));
+      for (int i = 0; i < NI; ++i) tf[k][i] = *(const half8*)(Tb + i * 2048 + (((4 * ks + g) ^ (r & 7)) << 4));
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) wf[ks][j] = *(const half8*)(Wb + (2 * j + ks) * 1024);
+      for (int j = 0; j < NJ; ++j) wf[k][j] = *(const half8*)(Wb + (2 * j + ks) * 1024);
     }
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
+    for (int k = 0; k < KS; ++k)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int i = 0; i < NI; ++i)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[ks][j], tf[ks][i], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[k][j], tf[k][i], acc[i][j], 0, 0, 0);
+  }
+  if constexpr (WK == 2) {
+    // the two waves of a tile trade halves of their sums through LDS: wave wk keeps
+    // the token blocks [wk NI/2, (wk + 1) NI/2), the even MFMA steps' sum first
+    constexpr int H = NI / 2;
+    static_assert(NI % 2 == 0 && WM * WN * 64 * NI * NJ * 16 <= NST * STAGE, "the exchange fits the stages");
+    f32x4* xc = (f32x4*)tsm + (size_t)(wm * WN + wn) * NI * NJ * 64 + lane;
+    __syncthreads();  // every stage is read out
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        if ((i < H) == (wk == 1)) xc[(i * NJ + j) * 64] = acc[i][j];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      if ((i < H) == (wk == 0)) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] += xc[(i * NJ + j) * 64];
+        const int tok = m0 + wm * TM + i * 16 + r;
+        if (tok < M)
+          tok_epilogue<EPI>(acc[i], [&](int j) { return n0 + wn * TN + 16 * j; }, g, tok, M, sp, out, ldo);
+      }
+    return;
   }
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
@@ -336,14 +369,14 @@ static hipError_t launch_pp(const f16* u, const f16* W, int M, int N, int K, voi
   return hipGetLastError();
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int NST>
+template <int EPI, int BM, int BN, int WM, int WN, int WK, int NST>
 static hipError_t launch_pipe(const f16* u, const f16* W, int M, int N, int K, void* out, int ldo, int splits,
                               hipStream_t s) {
   constexpr int LDS = NST * (BM + BN) * 128;
-  static const hipError_t lim = lds_limit(k_tok_pipe<EPI, BM, BN, WM, WN, NST>, LDS);
+  static const hipError_t lim = lds_limit(k_tok_pipe<EPI, BM, BN, WM, WN, WK, NST>, LDS);
   if (lim != hipSuccess) return lim;
-  hipLaunchKernelGGL((k_tok_pipe<EPI, BM, BN, WM, WN, NST>), dim3((N / BN) * ((M + BM - 1) / BM), splits),
-                     dim3(64 * WM * WN), LDS, s, u, W, M, N, K, out, ldo);
+  hipLaunchKernelGGL((k_tok_pipe<EPI, BM, BN, WM, WN, WK, NST>), dim3((N / BN) * ((M + BM - 1) / BM), splits),
+                     dim3(64 * WM * WN * WK), LDS, s, u, W, M, N, K, out, ldo);
   return hipGetLastError();
 }
 
@@ -352,13 +385,14 @@ static hipError_t tok_epi(int tile, const f16* u, const f16* W, int M, int N, in
                           hipStream_t s) {
   switch (tile) {
     case TT_256x256: return launch_pp<EPI>(u, W, M, N, K, out, ldo, splits, KvEpi{}, s);
-    case TT_128x256: return launch_pipe<EPI, 128, 256, 2, 4, 3>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_256x128: return launch_pipe<EPI, 256, 128, 4, 2, 3>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_128x128x2: return launch_pipe<EPI, 128, 128, 2, 2, 2>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_128x128: return launch_pipe<EPI, 128, 128, 4, 2, 4>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_64x128: return launch_pipe<EPI, 64, 128, 1, 4, 3>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_128x64: return launch_pipe<EPI, 128, 64, 2, 2, 3>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_64x256: return launch_pipe<EPI, 64, 256, 1, 8, 4>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_128x256: return launch_pipe<EPI, 128, 256, 2, 4, 1, 3>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_256x128: return launch_pipe<EPI, 256, 128, 4, 2, 1, 3>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_128x128x2: return launch_pipe<EPI, 128, 128, 2, 2, 2, 2>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_128x128: return launch_pipe<EPI, 128, 128, 4, 2, 1, 4>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_64x128: return launch_pipe<EPI, 64, 128, 1, 4, 1, 3>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_128x64: return launch_pipe<EPI, 128, 64, 2, 2, 1, 3>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_64x256: return launch_pipe<EPI, 64, 256, 1, 8, 1, 4>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_128x64w8: return launch_pipe<EPI, 128, 64, 2, 2, 2, 6>(u, W, M, N, K, out, ldo, splits, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -10,7 +10,7 @@ from test_gpu_kernels import EPI_RESID, EPI_STORE, EPI_SWIGLU, _dev, _f, _ptr, _
 
 pytestmark = pytest.mark.gpu
 EPI_PART = 3
-TILES = ((256, 256), (128, 256), (256, 128), (128, 128), (128, 128), (64, 128), (128, 64), (64, 256))
+TILES = ((256, 256), (128, 256), (256, 128), (128, 128), (128, 128), (64, 128), (128, 64), (64, 256), (128, 64))
 
 
 def _frag32(Wt):
@@ -74,4 +74,4 @@ def test_gemm_tokens_refusals(probe):  # noqa: F811
     assert call(5, EPI_STORE, 8, 128, 96, 1) != 0   # K not a multiple of 64
     assert call(5, EPI_STORE, 8, 128, 128, 2) != 0  # splits without partial sums
     assert call(5, EPI_PART, 8, 128, 128, 3) != 0   # more splits than K steps
-    assert call(8, EPI_STORE, 8, 128, 128, 1) != 0
+    assert call(len(TILES), EPI_STORE, 8, 128, 128, 1) != 0
