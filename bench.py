@@ -581,10 +581,10 @@ def main():
     if tr and tr[1]:  # HBM bytes over algorithmic bytes of the counted step (profiles/*_pmc.txt)
         roof["traffic_vs_algorithmic"] = round(tr[0] / tr[1], 3)
     if r["build"]:
-        roof["rebuild"] = {"kernel": "ams_ctx_build: k_gemm_big GEMMs + k_attn_prefill_mfma + row kernels",
+        roof["rebuild"] = {"kernel": "ams_ctx_build: k_tok_pp GEMMs + k_attn_prefill_mfma + row kernels",
                            **r["build"], "frac_vs_measured": round(r["build"]["achieved"] / peaks["mfma_f16_TFLOPs"], 4)}
     if r["extension"]:
-        roof["extension"] = {"kernel": "ams_ctx_append: k_gemm_big GEMMs (split-K O/down) + k_attn_extend + row kernels",
+        roof["extension"] = {"kernel": "ams_ctx_append: k_tok_pipe and k_tok_pp GEMMs (split-K O/down) + k_attn_extend + row kernels",
                              **r["extension"],
                              "frac_vs_measured": round(r["extension"]["achieved"] / peaks["mfma_f16_TFLOPs"], 4)}
     out = {

@@ -9,7 +9,7 @@ namespace ams {
 
 // Tile shapes (tokens x weight rows); see gemm_tokens.hip.
 enum TokTile {
-  TT_256x256 = 0, TT_128x256, TT_256x128, TT_128x128x2, TT_128x128, TT_64x128, TT_128x64, TT_64x256, TT_128x64w8, TT_COUNT
+  TT_256x256 = 0, TT_128x256, TT_256x128, TT_128x128x2, TT_128x128, TT_64x128, TT_128x64, TT_64x256, TT_COUNT
 };
 struct TokTileInfo {
   int bm, bn, per_cu;  // per_cu: workgroups a CU holds (LDS)
@@ -19,8 +19,7 @@ struct TokTileInfo {
 // workgroups on the CUs; 256 x 256 over many rounds (the clock drops under it).
 constexpr TokTileInfo TOK_TILES[TT_COUNT] = {
     {256, 256, 1, 1.50f, 1.60f}, {128, 256, 1, 1.00f, 1.08f}, {256, 128, 1, 1.00f, 1.08f}, {128, 128, 2, 0.85f, 1.06f},
-    {128, 128, 1, 0.62f, 0.62f}, {64, 128, 2, 0.52f, 0.82f},  {128, 64, 2, 0.52f, 0.82f},  {64, 256, 1, 0.72f, 0.72f},
-    {128, 64, 1, 0.44f, 0.44f},
+    {128, 128, 1, 0.62f, 0.62f}, {64, 128, 2, 0.52f, 0.82f},  {128, 64, 1, 0.44f, 0.44f},  {64, 256, 1, 0.72f, 0.72f},
 };
 
 // Tile shape of weight rows 0 .. main_n - 1 (all N of them where rest_tile is

@@ -298,6 +298,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_tok_pipe(const f16* __res
   for (int t = 0; t < KT; ++t) {
     if (t + NST - 2 < KT) wait_vm<(NST - 2) * LPW>();
     else wait_vm<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the stage that is refilled next is read out
     __builtin_amdgcn_s_barrier();
     if (t + NST - 1 < KT) dma(t + NST - 1);
     const unsigned char* cur = tsm + (t % NST) * STAGE;
@@ -390,9 +391,8 @@ static hipError_t tok_epi(int tile, const f16* u, const f16* W, int M, int N, in
     case TT_128x128x2: return launch_pipe<EPI, 128, 128, 2, 2, 2, 2>(u, W, M, N, K, out, ldo, splits, s);
     case TT_128x128: return launch_pipe<EPI, 128, 128, 4, 2, 1, 4>(u, W, M, N, K, out, ldo, splits, s);
     case TT_64x128: return launch_pipe<EPI, 64, 128, 1, 4, 1, 3>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_128x64: return launch_pipe<EPI, 128, 64, 2, 2, 1, 3>(u, W, M, N, K, out, ldo, splits, s);
     case TT_64x256: return launch_pipe<EPI, 64, 256, 1, 8, 1, 4>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_128x64w8: return launch_pipe<EPI, 128, 64, 2, 2, 2, 6>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_128x64: return launch_pipe<EPI, 128, 64, 2, 2, 2, 6>(u, W, M, N, K, out, ldo, splits, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -5,7 +5,7 @@ import os
 
 import pytest
 
-BN = (256, 256, 128, 128, 128, 128, 64, 256, 64)
+BN = (256, 256, 128, 128, 128, 128, 64, 256)
 
 
 @pytest.fixture(scope="module")

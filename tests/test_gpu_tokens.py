@@ -10,7 +10,7 @@ from test_gpu_kernels import EPI_RESID, EPI_STORE, EPI_SWIGLU, _dev, _f, _ptr, _
 
 pytestmark = pytest.mark.gpu
 EPI_PART = 3
-TILES = ((256, 256), (128, 256), (256, 128), (128, 128), (128, 128), (64, 128), (128, 64), (64, 256), (128, 64))
+TILES = ((256, 256), (128, 256), (256, 128), (128, 128), (128, 128), (64, 128), (128, 64), (64, 256))
 
 
 def _frag32(Wt):
