@@ -82,8 +82,10 @@ __global__ __launch_bounds__(256) void k_kv_append(const float* __restrict__ qkv
     const float2 cs = rope[(size_t)p * half + ii];
     const float a = k[h * dh + ii], c = k[h * dh + ii + half];
     T* dst = kslab + kv_slot(pg, H, h, p & (KV_PAGE - 1), dh);
-    st<T>(dst, ii, a * cs.x - c * cs.y);
-    st<T>(dst, ii + half, a * cs.y + c * cs.x);
+    float lo, hi;
+    rope_pair(a, c, cs.x, cs.y, lo, hi);
+    st<T>(dst, ii, lo);
+    st<T>(dst, ii + half, hi);
   }
   for (int e = threadIdx.x; e < d; e += blockDim.x) {
     const int h = e / dh, dd = e % dh;
@@ -137,8 +139,10 @@ __global__ __launch_bounds__(256) void k_kv_append_tab(const float* __restrict__
     half4v lo, hi;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      lo[j] = sat16(av[j] * cx[j] - cv[j] * cy[j]);
-      hi[j] = sat16(av[j] * cy[j] + cv[j] * cx[j]);
+      float l, u;
+      rope_pair(av[j], cv[j], cx[j], cy[j], l, u);
+      lo[j] = sat16(l);
+      hi[j] = sat16(u);
     }
     f16* dst = kslab + base + (size_t)h * KV_PAGE * dh;
     *(half4v*)(dst + ii) = lo;

@@ -64,6 +64,13 @@ __device__ __forceinline__ void split16(float v, f16* hi, f16* lo, size_t i) {
   if (lo) lo[i] = sat16(v - (float)h);
 }
 
+// The rotated pair (a, c) of a key at (cos, sin) = (cx, cy), roundings spelled out:
+// every kernel that writes a key gives it the same bits.
+__device__ __forceinline__ void rope_pair(float a, float c, float cx, float cy, float& lo, float& hi) {
+  lo = fmaf(a, cx, -(c * cy));
+  hi = fmaf(a, cy, c * cx);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

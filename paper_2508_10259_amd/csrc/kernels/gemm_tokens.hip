@@ -207,9 +207,10 @@ __global__ __launch_bounds__(512) void k_tok_pp(const f16* __restrict__ u, const
           half4v lo, hi;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float a = acc[i][j][e], c = acc[i][j + DP][e];
-            lo[e] = sat16(a * cx[e] - c * cy[e]);
-            hi[e] = sat16(a * cy[e] + c * cx[e]);
+            float l, u;
+            rope_pair(acc[i][j][e], acc[i][j + DP][e], cx[e], cy[e], l, u);
+            lo[e] = sat16(l);
+            hi[e] = sat16(u);
           }
           f16* kd = dst + (size_t)h * KV_PAGE * DH + dd;
           *(half4v*)kd = lo;
