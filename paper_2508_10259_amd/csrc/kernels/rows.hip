@@ -5,12 +5,9 @@
 
 namespace ams {
 
-// Threads per row of the norm kernels: 256, or 1024 for rows past 4,096 and where
-// rows of 1,024 and more are too few to fill the CUs and a row's chain of loads
-// sets the time (128 rows of 4,096, 8 splits: the residual reduction 9.0 -> 7.8 us;
-// the norm alone 4.7 us either way).  Both kernels take it, so they sum the squares
-// alike.
-static int norm_threads(int M, int d) { return d > 4096 || (d >= 1024 && M <= 256) ? 1024 : 256; }
+// Threads per row whose registers hold the row in the norm kernels: the sum of squares
+// runs over their elements, so a row's norm has the same bits in a pass of any length.
+static int norm_threads(int d) { return d <= 4096 ? 256 : 1024; }
 
 // One workgroup per token row (norm_threads); statistics in fp32.  Each thread loads its EPT (<= 16) elements before
 // reducing, so a row costs one memory round trip.
@@ -43,7 +40,7 @@ __global__ __launch_bounds__(1024) void k_rmsnorm(const float* __restrict__ h, i
 
 template <typename T>
 static hipError_t rmsnorm_t(const float* h, int M, int d, float eps, T* u, T* ulo, hipStream_t s) {
-  const int nt = norm_threads(M, d);
+  const int nt = norm_threads(d);
   const int ept = (d + nt - 1) / nt;  // <= 16 for d <= 16384
 #define AMS_RMS(E) hipLaunchKernelGGL((k_rmsnorm<T, E>), dim3(M), dim3(nt), 0, s, h, d, eps, u, ulo)
   if (ept <= 1) AMS_RMS(1);
@@ -77,7 +74,11 @@ hipError_t rmsnorm(int ct, const float* h, int M, int d, float eps, void* u, hip
 // of G, each group's loads for all the thread's elements issued together;
 // a group's last loads past the split count read the last split again and are
 // not added.
-template <int EPT, int S>
+// WIDE: 1,024 threads on a row of at most 4,096, where rows are too few to fill the
+// CUs and a row's chain of loads sets the time; the first 256 threads then take the
+// squares from LDS, in the order of 256 threads' registers (128 rows of 4,096, 16
+// splits: 12.9 -> 9.2 us).
+template <int EPT, int S, bool WIDE>
 __global__ __launch_bounds__(1024) void k_resid_norm(const float* __restrict__ part, int splits, int d, float eps,
                                                      float* __restrict__ h, f16* __restrict__ u) {
   __shared__ float red[16];
@@ -119,6 +120,7 @@ __global__ __launch_bounds__(1024) void k_resid_norm(const float* __restrict__ p
           for (int e = 0; e < EPT; ++e) acc[e] += q[e][j];
     }
   }
+  extern __shared__ float xs[];  // WIDE: the new row
   float ss = 0.f;
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
@@ -126,10 +128,23 @@ __global__ __launch_bounds__(1024) void k_resid_norm(const float* __restrict__ p
     if (i < d) {
       x[e] += acc[e];
       h[base + i] = x[e];
+      if constexpr (WIDE) xs[i] = x[e];
     }
   }
+  if constexpr (WIDE) {
+    __syncthreads();
+    if (threadIdx.x < 256) {
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) ss = fmaf(x[e], x[e], ss);
+      for (int e = 0; e < 4 * EPT; ++e) {
+        const int i = threadIdx.x + e * 256;
+        const float v = i < d ? xs[i] : 0.f;
+        ss = fmaf(v, v, ss);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) ss = fmaf(x[e], x[e], ss);
+  }
   const float tot = block_sum(ss, red);
   const float rs = 1.0f / sqrtf(tot / (float)d + eps);
 #pragma unroll
@@ -139,11 +154,13 @@ __global__ __launch_bounds__(1024) void k_resid_norm(const float* __restrict__ p
   }
 }
 
-template <int EPT>
-static void launch_resid_norm(const float* part, int splits, int M, int d, int nt, float* h, float eps, void* u,
+template <int EPT, bool WIDE = false>
+static void launch_resid_norm(const float* part, int splits, int M, int d, float* h, float eps, void* u,
                               hipStream_t s) {
-#define AMS_RN(S_) \
-  hipLaunchKernelGGL((k_resid_norm<EPT, S_>), dim3(M), dim3(nt), 0, s, part, splits, d, eps, h, (f16*)u)
+  const int nt = WIDE ? 1024 : norm_threads(d);
+#define AMS_RN(S_)                                                                                          \
+  hipLaunchKernelGGL((k_resid_norm<EPT, S_, WIDE>), dim3(M), dim3(nt), WIDE ? d * 4 : 0, s, part, splits, d, eps, h, \
+                     (f16*)u)
   // (EPT * S partial sums in registers: at most 64, within the 128 VGPRs of 1,024 threads)
   switch (EPT * splits <= 64 ? splits : 0) {
     case 2: AMS_RN(2); break;
@@ -158,13 +175,18 @@ static void launch_resid_norm(const float* part, int splits, int M, int d, int n
 hipError_t resid_norm(const float* part, int splits, int M, int d, float* h, float eps, void* u, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (splits < 1) return hipErrorInvalidValue;
-  const int nt = norm_threads(M, d);  // as rmsnorm: the same sum of squares
-  const int ept = (d + nt - 1) / nt;
-  if (ept <= 1) launch_resid_norm<1>(part, splits, M, d, nt, h, eps, u, s);
-  else if (ept <= 2) launch_resid_norm<2>(part, splits, M, d, nt, h, eps, u, s);
-  else if (ept <= 4) launch_resid_norm<4>(part, splits, M, d, nt, h, eps, u, s);
-  else if (ept <= 8) launch_resid_norm<8>(part, splits, M, d, nt, h, eps, u, s);
-  else if (ept <= 16) launch_resid_norm<16>(part, splits, M, d, nt, h, eps, u, s);
+  if (d >= 1024 && d <= 4096 && M <= 256) {
+    if (d <= 1024) launch_resid_norm<1, true>(part, splits, M, d, h, eps, u, s);
+    else if (d <= 2048) launch_resid_norm<2, true>(part, splits, M, d, h, eps, u, s);
+    else launch_resid_norm<4, true>(part, splits, M, d, h, eps, u, s);
+    return hipGetLastError();
+  }
+  const int nt = norm_threads(d), ept = (d + nt - 1) / nt;
+  if (ept <= 1) launch_resid_norm<1>(part, splits, M, d, h, eps, u, s);
+  else if (ept <= 2) launch_resid_norm<2>(part, splits, M, d, h, eps, u, s);
+  else if (ept <= 4) launch_resid_norm<4>(part, splits, M, d, h, eps, u, s);
+  else if (ept <= 8) launch_resid_norm<8>(part, splits, M, d, h, eps, u, s);
+  else if (ept <= 16) launch_resid_norm<16>(part, splits, M, d, h, eps, u, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

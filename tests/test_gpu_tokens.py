@@ -75,3 +75,21 @@ def test_gemm_tokens_refusals(probe):  # noqa: F811
     assert call(5, EPI_STORE, 8, 128, 128, 2) != 0  # splits without partial sums
     assert call(5, EPI_PART, 8, 128, 128, 3) != 0   # more splits than K steps
     assert call(len(TILES), EPI_STORE, 8, 128, 128, 1) != 0
+
+
+@pytest.mark.parametrize("d,splits", [(1024, 2), (1152, 5), (2048, 8), (4096, 1), (4096, 16), (5120, 4)])
+def test_norms_same_bits(probe, d, splits):  # noqa: F811
+    """A row's norm has the same bits in a pass of any length, alone and after the residual reduction."""
+    import torch
+    log(f"norms d={d} splits={splits}")
+    part = torch.from_numpy(W.random_gaussian((splits, 400, d), 117, d, dtype="f32")).cuda()
+    h0 = torch.from_numpy(W.random_gaussian((400, d), 118, d, dtype="f32")).cuda()
+    out = {}
+    for M in (400, 256, 65, 3):
+        h, p = h0[:M].clone(), part[:, :M].contiguous()
+        un, ur = (torch.empty((M, d), dtype=torch.float16, device="cuda") for _ in range(2))
+        eps = C.c_float(1e-5)
+        assert probe.ams_probe_rmsnorm(2, _ptr(h), M, d, eps, _ptr(un), None, _stream()) == 0
+        assert probe.ams_probe_resid_norm(_ptr(p), splits, M, d, _ptr(h), eps, _ptr(ur), _stream()) == 0
+        out[M] = (un, ur, h)
+        assert all(torch.equal(a, b[:M]) for a, b in zip(out[M], out[400])), M
