@@ -330,8 +330,8 @@ static hipError_t tokens_resid(Ctx& c, const void* x, const void* W, const void*
     return e;
   }
   if (tiled_f16(md, M)) {
-    const TokPlan p = tok_plan(M, d, K, true);
-    if (p.splits == 1) return gemm_tokens_tile(p.tile, EPI_RESID, x, Wf, M, d, K, c.h(), d, 1, s);
+    const TokPlan p = tok_resid_plan(M, d, K);
+    if (p.splits == 1) return gemm_tokens_tile(p.tile, EPI_RESID, x, Wf, M, d, K, c.h(), d, 1, s, p.segs);
     hipError_t e = gemm_tokens_tile(p.tile, EPI_PART, x, Wf, M, d, K, c.kpart(), d, p.splits, s);
     if (e == hipSuccess) e = resid_norm(c.kpart(), p.splits, M, d, c.h(), md.cfg.rms_eps, c.u(), s);
     normed = e == hipSuccess;

@@ -1,6 +1,7 @@
 // fp16 projections of token passes (more than 64 tokens: prefix builds,
 // observation extensions, flow chunks): y = u W^T with u row-major and W in MFMA
-// fragment order (frag_pack), fp32 accumulation in K order, fused epilogues.
+// fragment order (frag_pack), fp32 accumulation in K order on every tile shape, so
+// that the shape a pass's token count picks does not show in its results; fused epilogues.
 //
 // Both kernels move their tiles from global memory straight into LDS
 // (global_load_lds_dwordx4: a wave instruction fills 1 KB, lane i the i-th 16
@@ -12,7 +13,7 @@
 //
 //  * k_tok_pp: 256 x 256 tiles, one workgroup of 8 waves per CU, for passes with
 //    enough of them.  Bound by the MFMA rate.
-//  * k_tok_pipe: smaller tiles with up to four K steps of loads in flight, for
+//  * k_tok_pipe: smaller tiles with one to five K steps of loads in flight, for
 //    passes whose 256 x 256 tiles would leave CUs idle.  Bound by the latency and
 //    rate of the operand loads.
 #include <type_traits>
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(512) void k_tok_pp(const f16* __restrict__ u, const
 }
 
 // ----------------------------------------------------------------------------
-// BM tokens x BN weight rows, WM x WN x WK waves, K steps of 64 through NST LDS stages
+// BM tokens x BN weight rows, WM x WN waves, K steps of 64 through NST LDS stages
 // with one barrier per step: a wave waits for its own loads of the step (issued
 // NST - 1 steps earlier), the barrier makes every wave's visible and says that the
 // stage of the step before is read out, and the loads NST - 1 steps ahead go into
@@ -239,24 +240,23 @@ __global__ __launch_bounds__(512) void k_tok_pp(const f16* __restrict__ u, const
 // whole memory round trip, 1.2 us, whatever its size.  Measured on the 7B
 // shapes: 128 tokens QKV 82 -> 34 us, gate|up 82 -> 45 us; 288 tokens QKV 73 -> 49;
 // 600 tokens QKV 89 -> 68 us, gate|up 180 -> 130 us, O 45 -> 30, down 100 -> 65.
-// WK = 2: two waves share a wave tile, each with one of a K step's two MFMA steps, and
-// trade halves of their sums at the end.  Twice the waves on the same LDS traffic: one
-// 128 x 64 workgroup on a CU kept four waves, one per SIMD, that all waited for the
-// same stage (three of them; eight waves and six stages: QKV 34.0 -> 31.5 us at 128 tokens
-// of the 7B width, 30.9 -> 26.5 at 72; 288 tokens of d = 1024 10.0 -> 9.1), and two
-// 128 x 128 workgroups of four gain 1-2% (QKV 288 tokens 59.9 -> 58.5, d = 1024 and 2,240
-// tokens 21.8 -> 21.3).  The tiles whose one workgroup has eight waves anyway do not.
-template <int EPI, int BM, int BN, int WM, int WN, int WK, int NST>
-__global__ __launch_bounds__(64 * WM * WN * WK) void k_tok_pipe(const f16* __restrict__ u, const f16* __restrict__ W, int M,
-                                                           int N, int K, void* __restrict__ out, int ldo) {
-  constexpr int NW = WM * WN * WK, TM = BM / WM, TN = BN / WN, NI = TM / 16, NJ = TN / 16;
+// The 128 x 64 tile and the two 128 x 128 workgroups of a CU have eight waves of 32
+// x 32 and 64 x 32: four left a SIMD one wave, which waited for the same stage as the
+// others (QKV of the 7B width at 128 tokens 34.0 -> 31.9 us, 30.9 -> 28.5 at 72; 288
+// tokens of two 128 x 128 workgroups 60.9 -> 60.0).
+// SEG (a residual projection whose K ranges one workgroup adds): each range's sums
+// start from zero and are added in order, as the reduction of partial sums adds them.
+template <int EPI, int BM, int BN, int WM, int WN, int NST, bool SEG>
+__global__ __launch_bounds__(64 * WM * WN) void k_tok_pipe(const f16* __restrict__ u, const f16* __restrict__ W, int M,
+                                                           int N, int K, void* __restrict__ out, int ldo, int segs) {
+  constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, NI = TM / 16, NJ = TN / 16;
   constexpr int AB = BM / 8, BB = BN / 8, LPW = (AB + BB) / NW;  // 1 KB blocks of a stage, loads per wave
   constexpr int STAGE = (AB + BB) * 1024;
   static_assert((AB + BB) % NW == 0, "every wave issues as many loads per stage");
   static_assert(EPI != EPI_SWIGLU || NJ % 2 == 0, "gate and up strips come in pairs");
   extern __shared__ __attribute__((aligned(16))) unsigned char tsm[];  // [stage][AB token | BB weight blocks]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 15, g = lane >> 4, wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+  const int r = lane & 15, g = lane >> 4, wm = wave / WN, wn = wave % WN;
   int m0, n0;
   tok_tile<BM, BN>(M, N, m0, n0);
   const int alast = M - 1 - m0;
@@ -293,6 +293,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_tok_pipe(const f16* __res
   for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 tot[SEG ? NI : 1][SEG ? NJ : 1];
+  int seg = 1, seg_end = KT / segs;  // the range this K step lies in, and its end
+  if constexpr (SEG)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) tot[i][j] = acc[i][j];
 #pragma unroll
   for (int t = 0; t < NST - 1; ++t)
     if (t < KT) dma(t);
@@ -305,53 +312,43 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void k_tok_pipe(const f16* __res
     const unsigned char* cur = tsm + (t % NST) * STAGE;
     const unsigned char* Tb = cur + (wm * TM + r) * 128;
     const unsigned char* Wb = cur + AB * 1024 + wn * NJ * 2048 + lane * 16;
-    constexpr int KS = 2 / WK;  // MFMA steps of 32 that this wave takes of the K step
-    half8 tf[KS][NI], wf[KS][NJ];
+    half8 tf[2][NI], wf[2][NJ];
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const int ks = WK == 2 ? wk : k;
+    for (int k = 0; k < 2; ++k) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i) tf[k][i] = *(const half8*)(Tb + i * 2048 + (((4 * ks + g) ^ (r & 7)) << 4));
+      for (int i = 0; i < NI; ++i) tf[k][i] = *(const half8*)(Tb + i * 2048 + (((4 * k + g) ^ (r & 7)) << 4));
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) wf[k][j] = *(const half8*)(Wb + (2 * j + ks) * 1024);
+      for (int j = 0; j < NJ; ++j) wf[k][j] = *(const half8*)(Wb + (2 * j + k) * 1024);
     }
 #pragma unroll
-    for (int k = 0; k < KS; ++k)
+    for (int k = 0; k < 2; ++k)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int i = 0; i < NI; ++i)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[k][j], tf[k][i], acc[i][j], 0, 0, 0);
-  }
-  if constexpr (WK == 2) {
-    // the two waves of a tile trade halves of their sums through LDS: wave wk keeps
-    // the token blocks [wk NI/2, (wk + 1) NI/2), the even MFMA steps' sum first
-    constexpr int H = NI / 2;
-    static_assert(NI % 2 == 0 && WM * WN * 64 * NI * NJ * 16 <= NST * STAGE, "the exchange fits the stages");
-    f32x4* xc = (f32x4*)tsm + (size_t)(wm * WN + wn) * NI * NJ * 64 + lane;
-    __syncthreads();  // every stage is read out
+    if constexpr (SEG) {
+      if (t + 1 == seg_end) {
+        seg_end = ++seg * KT / segs;
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        if ((i < H) == (wk == 1)) xc[(i * NJ + j) * 64] = acc[i][j];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-      if ((i < H) == (wk == 0)) {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] += xc[(i * NJ + j) * 64];
-        const int tok = m0 + wm * TM + i * 16 + r;
-        if (tok < M)
-          tok_epilogue<EPI>(acc[i], [&](int j) { return n0 + wn * TN + 16 * j; }, g, tok, M, sp, out, ldo);
+          for (int j = 0; j < NJ; ++j) {
+            tot[i][j] += acc[i][j];
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
       }
-    return;
+    }
   }
+  auto& y = [&]() -> f32x4(&)[NI][NJ] {
+    if constexpr (SEG) return tot;
+    else return acc;
+  }();
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int tok = m0 + wm * TM + i * 16 + r;
     if (tok < M)
-      tok_epilogue<EPI>(acc[i], [&](int j) { return n0 + wn * TN + 16 * j; }, g, tok, M, sp, out, ldo);
+      tok_epilogue<EPI>(y[i], [&](int j) { return n0 + wn * TN + 16 * j; }, g, tok, M, sp, out, ldo);
   }
 }
 
@@ -371,52 +368,56 @@ static hipError_t launch_pp(const f16* u, const f16* W, int M, int N, int K, voi
   return hipGetLastError();
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int WK, int NST>
+template <int EPI, int BM, int BN, int WM, int WN, int NST, bool SEG>
 static hipError_t launch_pipe(const f16* u, const f16* W, int M, int N, int K, void* out, int ldo, int splits,
-                              hipStream_t s) {
+                              int segs, hipStream_t s) {
   constexpr int LDS = NST * (BM + BN) * 128;
-  static const hipError_t lim = lds_limit(k_tok_pipe<EPI, BM, BN, WM, WN, WK, NST>, LDS);
+  static const hipError_t lim = lds_limit(k_tok_pipe<EPI, BM, BN, WM, WN, NST, SEG>, LDS);
   if (lim != hipSuccess) return lim;
-  hipLaunchKernelGGL((k_tok_pipe<EPI, BM, BN, WM, WN, WK, NST>), dim3((N / BN) * ((M + BM - 1) / BM), splits),
-                     dim3(64 * WM * WN * WK), LDS, s, u, W, M, N, K, out, ldo);
+  hipLaunchKernelGGL((k_tok_pipe<EPI, BM, BN, WM, WN, NST, SEG>), dim3((N / BN) * ((M + BM - 1) / BM), splits),
+                     dim3(64 * WM * WN), LDS, s, u, W, M, N, K, out, ldo, segs);
   return hipGetLastError();
 }
 
-template <int EPI>
+template <int EPI, bool SEG = false>
 static hipError_t tok_epi(int tile, const f16* u, const f16* W, int M, int N, int K, void* out, int ldo, int splits,
-                          hipStream_t s) {
+                          int segs, hipStream_t s) {
   switch (tile) {
-    case TT_256x256: return launch_pp<EPI>(u, W, M, N, K, out, ldo, splits, KvEpi{}, s);
-    case TT_128x256: return launch_pipe<EPI, 128, 256, 2, 4, 1, 3>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_256x128: return launch_pipe<EPI, 256, 128, 4, 2, 1, 3>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_128x128x2: return launch_pipe<EPI, 128, 128, 2, 2, 2, 2>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_128x128: return launch_pipe<EPI, 128, 128, 4, 2, 1, 4>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_64x128: return launch_pipe<EPI, 64, 128, 1, 4, 1, 3>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_64x256: return launch_pipe<EPI, 64, 256, 1, 8, 1, 4>(u, W, M, N, K, out, ldo, splits, s);
-    case TT_128x64: return launch_pipe<EPI, 128, 64, 2, 2, 2, 6>(u, W, M, N, K, out, ldo, splits, s);
+    case TT_256x256:
+      if constexpr (!SEG) return launch_pp<EPI>(u, W, M, N, K, out, ldo, splits, KvEpi{}, s);
+      return hipErrorInvalidValue;
+    case TT_128x256: return launch_pipe<EPI, 128, 256, 2, 4, 3, SEG>(u, W, M, N, K, out, ldo, splits, segs, s);
+    case TT_256x128: return launch_pipe<EPI, 256, 128, 4, 2, 3, SEG>(u, W, M, N, K, out, ldo, splits, segs, s);
+    case TT_128x128x2: return launch_pipe<EPI, 128, 128, 2, 4, 2, SEG>(u, W, M, N, K, out, ldo, splits, segs, s);
+    case TT_128x128: return launch_pipe<EPI, 128, 128, 4, 2, 4, SEG>(u, W, M, N, K, out, ldo, splits, segs, s);
+    case TT_64x128: return launch_pipe<EPI, 64, 128, 1, 4, 3, SEG>(u, W, M, N, K, out, ldo, splits, segs, s);
+    case TT_64x256: return launch_pipe<EPI, 64, 256, 1, 8, 4, SEG>(u, W, M, N, K, out, ldo, splits, segs, s);
+    case TT_128x64: return launch_pipe<EPI, 128, 64, 4, 2, 6, SEG>(u, W, M, N, K, out, ldo, splits, segs, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 hipError_t gemm_tokens_tile(int tile, int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo,
-                            int splits, hipStream_t s) {
+                            int splits, hipStream_t s, int segs) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (tile < 0 || tile >= TT_COUNT || N % TOK_TILES[tile].bn != 0 || K % 64 != 0 || splits < 1 || splits > K / 64 ||
-      (splits > 1 && epi != EPI_PART))
+      (splits > 1 && epi != EPI_PART) || segs < 1 || segs > K / 64 || (segs > 1 && epi != EPI_RESID))
     return hipErrorInvalidValue;
   const f16 *x = (const f16*)u, *w = (const f16*)Wf;
   switch (epi) {
-    case EPI_STORE: return tok_epi<EPI_STORE>(tile, x, w, M, N, K, out, ldo, 1, s);
-    case EPI_RESID: return tok_epi<EPI_RESID>(tile, x, w, M, N, K, out, ldo, 1, s);
-    case EPI_SWIGLU: return tok_epi<EPI_SWIGLU>(tile, x, w, M, N, K, out, ldo, 1, s);
-    case EPI_PART: return tok_epi<EPI_PART>(tile, x, w, M, N, K, out, N, splits, s);
+    case EPI_STORE: return tok_epi<EPI_STORE>(tile, x, w, M, N, K, out, ldo, 1, 1, s);
+    case EPI_RESID:
+      if (segs > 1) return tok_epi<EPI_RESID, true>(tile, x, w, M, N, K, out, ldo, 1, segs, s);
+      return tok_epi<EPI_RESID>(tile, x, w, M, N, K, out, ldo, 1, 1, s);
+    case EPI_SWIGLU: return tok_epi<EPI_SWIGLU>(tile, x, w, M, N, K, out, ldo, 1, 1, s);
+    case EPI_PART: return tok_epi<EPI_PART>(tile, x, w, M, N, K, out, N, splits, 1, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 hipError_t gemm_tokens(int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo,
                        hipStream_t s) {
-  const TokPlan p = tok_plan(M, N, K, false);
+  const TokPlan p = tok_plan(M, N, K, 1, true);
   hipError_t e = gemm_tokens_tile(p.tile, epi, u, Wf, M, p.main_n, K, out, ldo, 1, s);
   if (e != hipSuccess || p.rest_tile < 0) return e;
   // the weight rows past main_n (output columns main_n / 2 on for SwiGLU)
@@ -427,7 +428,7 @@ hipError_t gemm_tokens(int epi, const void* u, const void* Wf, int M, int N, int
 
 bool gemm_qkv_fusable(int M, int N, int dh, int d) {
   if (M <= 64 || (dh != 64 && dh != 128) || d % 256 != 0 || N != 3 * d) return false;
-  return (size_t)(N / 256) * ((M + 255) / 256) > 256 && tok_plan(M, N, d, false, false).tile == TT_256x256;
+  return (size_t)(N / 256) * ((M + 255) / 256) > 256 && tok_plan(M, N, d, 1, false).tile == TT_256x256;
 }
 
 hipError_t gemm_qkv_kv(const void* u, const void* Wf, int M, int K, float* qkv, const KvEpi& kv, hipStream_t s) {

@@ -128,10 +128,12 @@ hipError_t part_resid(const float* part, int splits, int M, int N, float* h, voi
 // picks, or on a given one (gemm_plan.h; N a multiple of its width, K of 64).
 // EPI_PART (gemm_tokens_tile): split-K partial sums, part[s][m][n] = the s-th of
 // `splits` equal ranges of K steps of 64 of sum_k u[m][k] W[n][k], splits * M * N
-// floats, which part_resid or resid_norm add to the residual.
+// floats, which part_resid or resid_norm add to the residual.  segs > 1 (EPI_RESID): one
+// workgroup per tile adds `segs` such ranges itself, the same sums in the same order.
+// Every tile gives the same bits.
 hipError_t gemm_tokens(int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo, hipStream_t s);
 hipError_t gemm_tokens_tile(int tile, int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo,
-                            int splits, hipStream_t s);
+                            int splits, hipStream_t s, int segs = 1);
 
 // Decode GEMV with the preceding RMSNorm fused (fp16, M <= 16), on the fp16
 // copy x = hhi (+ hlo, its rounding error, when non-NULL) of the residual rows:

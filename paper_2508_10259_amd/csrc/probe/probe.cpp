@@ -59,9 +59,15 @@ int ams_probe_gemm_tokens(int tile, int epi, const void* u, const void* Wf, int 
                           int splits, void* stream) {
   return (int)ams::gemm_tokens_tile(tile, epi, u, Wf, M, N, K, out, ldo, splits, (hipStream_t)stream);
 }
+// a residual projection whose K ranges one workgroup per tile adds
+int ams_probe_gemm_tokens_segs(int tile, const void* u, const void* Wf, int M, int N, int K, float* h, int segs,
+                               void* stream) {
+  return (int)ams::gemm_tokens_tile(tile, ams::EPI_RESID, u, Wf, M, N, K, h, N, 1, (hipStream_t)stream, segs);
+}
+int ams_probe_tok_resid_splits(int M, int N, int K) { return ams::tok_resid_splits(M, N, K); }
 // out[0..3]: tile, splits, weight rows on it, tile of the rest (-1: none)
 void ams_probe_tok_plan(int M, int N, int K, int split, int32_t* out) {
-  const ams::TokPlan p = ams::tok_plan(M, N, K, split != 0);
+  const ams::TokPlan p = split ? ams::tok_resid_plan(M, N, K) : ams::tok_plan(M, N, K, 1, true);
   out[0] = p.tile; out[1] = p.splits; out[2] = p.main_n; out[3] = p.rest_tile;
 }
 size_t ams_probe_tok_part_floats(int N, int K, int T) { return ams::tok_part_floats(N, K, T); }

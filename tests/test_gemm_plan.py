@@ -36,3 +36,14 @@ def test_tok_plan(probe, d, F):
                 else:
                     assert splits == 1 and (rest == -1) == (main_n == N)
                     assert rest == -1 or ((N - main_n) % BN[rest] == 0 and main_n % 32 == 0)
+
+
+@pytest.mark.parametrize("M,N,K,splits", [
+    (64, 4096, 4096, 1), (65, 4096, 4096, 8), (128, 4096, 11008, 16), (256, 4096, 11008, 16), (257, 4096, 11008, 8),
+    (288, 4096, 4096, 8), (600, 4096, 11008, 6), (1024, 4096, 4096, 4), (2240, 1024, 1024, 2), (2240, 1024, 4096, 8),
+    (2304, 4096, 11008, 2), (2305, 4096, 11008, 1), (19200, 4096, 4096, 1), (300, 384, 640, 1)])
+def test_resid_splits(probe, M, N, K, splits):
+    """The K ranges whose sums a residual projection adds are part of its result: they follow the
+    shape alone (tiles of 256 x 256 times splits about 256, at least 8 K steps each), whatever the
+    tile plan or the room for partial sums."""
+    assert probe.ams_probe_tok_resid_splits(M, N, K) == splits

@@ -77,6 +77,33 @@ def test_gemm_tokens_refusals(probe):  # noqa: F811
     assert call(len(TILES), EPI_STORE, 8, 128, 128, 1) != 0
 
 
+@pytest.mark.parametrize("M,K,segs", [(65, 1024, 3), (130, 64, 1), (300, 1984, 8), (513, 4096, 5)])
+def test_tiles_same_bits(probe, M, K, segs):  # noqa: F811
+    """Every tile shape gives the same bits, and so do a residual projection whose K ranges one
+    workgroup adds and the reduction of the same ranges' partial sums."""
+    import torch
+    N = 768
+    log(f"same bits M={M} K={K} segs={segs}")
+    ud, wd = _dev(_rand((M, K), 114, M, K), "f16"), _dev(_frag32(_rand((N, K), 115, N, K, std=0.05)), "f16")
+    h0 = torch.from_numpy(W.random_gaussian((M, N), 116, M, dtype="f32")).cuda()
+    y0 = hp = None
+    for tile in range(len(TILES)):
+        y, h, part = torch.empty_like(h0), h0.clone(), torch.empty((segs, M, N), device="cuda")
+        assert probe.ams_probe_gemm_tokens(tile, EPI_STORE, _ptr(ud), _ptr(wd), M, N, K, _ptr(y), N, 1, _stream()) == 0
+        assert probe.ams_probe_gemm_tokens(tile, EPI_PART, _ptr(ud), _ptr(wd), M, N, K, _ptr(part), N, segs,
+                                           _stream()) == 0
+        assert probe.ams_probe_part_resid(_ptr(part), segs, M, N, _ptr(h), None, None, _stream()) == 0
+        y0, hp = (y, h) if y0 is None else (y0, hp)
+        assert torch.equal(y, y0) and torch.equal(h, hp), TILES[tile]
+        h = h0.clone()
+        rc = probe.ams_probe_gemm_tokens_segs(tile, _ptr(ud), _ptr(wd), M, N, K, _ptr(h), segs, _stream())
+        if tile == 0 and segs > 1:  # no registers for the second accumulator
+            assert rc != 0
+        else:
+            assert rc == 0 and torch.equal(h, hp), TILES[tile]
+    assert probe.ams_probe_gemm_tokens_segs(4, _ptr(ud), _ptr(wd), M, N, K, _ptr(h), K // 64 + 1, _stream()) != 0
+
+
 @pytest.mark.parametrize("d,splits", [(1024, 2), (1152, 5), (2048, 8), (4096, 1), (4096, 16), (5120, 4)])
 def test_norms_same_bits(probe, d, splits):  # noqa: F811
     """A row's norm has the same bits in a pass of any length, alone and after the residual reduction."""
