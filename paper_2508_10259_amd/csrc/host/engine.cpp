@@ -27,18 +27,18 @@ static bool fused_norm(const Ctx& c, int rows) { return c.model->ct == DT_F16 &&
 // fp32 passes of up to 64 tokens run gemv_f32, which applies the RMSNorm itself.
 static bool short_f32(const Model& md, int M) { return md.ct == DT_F32 && M <= 64; }
 
-// Projections (N x K) of an fp16 token pass of up to 64 tokens that run the wide
-// GEMM: from 10 M weights on (4 M for the residual ones, whose K is split), where
-// the weight stream sets the pace (7B, 16 tokens: QKV 30.6 -> 20.0 us, gate|up 47.0
-// -> 32.0, down with the norm 30.0 -> 21.9; 64 tokens: 70.5 -> 26.3, 114 -> 39, 69 ->
-// 28.5).  Below, the skinny GEMV's single launch wins (d = 1024, 16 tokens: QKV 5.0
-// against 6.9 us, gate|up 6.4 against 8.9).
-static bool short_wide(const Model& md, int M, int N, int K, bool resid) {
-  return md.ct == DT_F16 && M <= 64 && (size_t)N * K >= (resid ? 4000000u : 10000000u);
+// K splits of a projection (N x K) of an fp16 token pass of 33 to 64 tokens that runs
+// the wide GEMM, 0 where it runs gemm_tokens_short: the wide GEMM from 10 M weights on
+// (4 M for the residual ones), where every strip of the short form would read the tokens
+// again (7B, 64 tokens: QKV 54.6 -> 26.8 us, gate|up 60.8 -> 37.6, down 52.1 -> 25.8).
+// Up to 32 tokens and on smaller weights the short form's single launch is as fast
+// or close (7B, 16 tokens: QKV 22.8 against 20.4, O 9.1 against 10.8, down 19.9 against
+// 18.8; 32 tokens: 29.8 against 22.4).
+static int short_wide(const Ctx& c, int M, int N, int K, bool resid) {
+  if (c.model->ct != DT_F16 || M <= 32 || M > 64 || (size_t)N * K < (resid ? 4000000u : 10000000u)) return 0;
+  const int S = decode_wsplit(N, K, M);
+  return (size_t)S * M * N <= c.lay.kpart_floats ? S : 0;
 }
-
-// fp16 token passes longer than that run gemm_tokens on the fragment-ordered weights.
-static bool tiled_f16(const Model& md, int M) { return md.ct == DT_F16 && M > 64; }
 
 // h += x W^T of a short fp32 pass, K split over more workgroups for long rows.
 static hipError_t resid_f32(const Ctx& c, const void* x, const void* W, int M, int K, float* h, hipStream_t s) {
@@ -319,32 +319,36 @@ static hipError_t tokens_resid(Ctx& c, const void* x, const void* W, const void*
   const int d = md.cfg.d_model;
   normed = false;
   if (short_f32(md, M)) return resid_f32(c, x, W, M, K, c.h(), s);
-  if (short_wide(md, M, d, K, true)) {
-    const int S = decode_wsplit(d, K, M);
-    if (wide_fused_reduce(M))
-      return gemm_wide_reduce(EPI_RESID, x, nullptr, Wf, M, d, K, S, c.kpart(), c.wcnt(), nullptr, nullptr, 0, c.h(),
-                              nullptr, nullptr, nullptr, nullptr, 0.f, s);
-    hipError_t e = gemm_wide(x, nullptr, Wf, M, d, K, S, c.kpart(), s);
-    if (e == hipSuccess) e = resid_norm(c.kpart(), S, M, d, c.h(), md.cfg.rms_eps, c.u(), s);
-    normed = e == hipSuccess;
-    return e;
-  }
-  if (tiled_f16(md, M)) {
-    const TokPlan p = tok_resid_plan(M, d, K);
+  if (md.ct == DT_F32) return gemm(DT_F32, EPI_RESID, x, W, M, d, K, c.h(), d, s);
+  int splits = 0;  // partial sums are in kpart
+  hipError_t e = hipSuccess;
+  if (M > 64) {
+    const TokPlan p = tok_resid_plan(M, d, K, c.lay.kpart_floats);
     if (p.splits == 1) return gemm_tokens_tile(p.tile, EPI_RESID, x, Wf, M, d, K, c.h(), d, 1, s, p.segs);
-    hipError_t e = gemm_tokens_tile(p.tile, EPI_PART, x, Wf, M, d, K, c.kpart(), d, p.splits, s);
-    if (e == hipSuccess) e = resid_norm(c.kpart(), p.splits, M, d, c.h(), md.cfg.rms_eps, c.u(), s);
-    normed = e == hipSuccess;
-    return e;
+    splits = p.splits;
+    e = gemm_tokens_tile(p.tile, EPI_PART, x, Wf, M, d, K, c.kpart(), d, splits, s);
+  } else {
+    splits = short_wide(c, M, d, K, true);
+    if (splits == 0) return gemm_tokens_short(EPI_RESID, x, Wf, M, d, K, c.h(), d, s);
+    e = gemm_wide(x, nullptr, Wf, M, d, K, splits, c.kpart(), s);
   }
-  return gemm(md.ct, EPI_RESID, x, W, M, d, K, c.h(), d, s);
+  if (e == hipSuccess) e = resid_norm(c.kpart(), splits, M, d, c.h(), md.cfg.rms_eps, c.u(), s);
+  normed = e == hipSuccess;
+  return e;
 }
 
-// A projection of u on the wide GEMM (short_wide).
-static hipError_t short_proj(const Ctx& c, int epi, const void* Wf, int M, int N, int K, void* out, int ldo,
-                             hipStream_t s) {
-  const int S = decode_wsplit(N, K, M);
-  if (epi == EPI_SWIGLU ? S == 1 : wide_fused_reduce(M))
+// A projection of u over the M tokens of a token pass (fp32 passes of up to 64 tokens:
+// of h, which gemv_f32 normalises itself).
+static hipError_t tokens_proj(const Ctx& c, int epi, const void* W, const void* Wf, int M, int N, int K, void* out,
+                              int ldo, hipStream_t s) {
+  const Model& md = *c.model;
+  if (short_f32(md, M))
+    return gemv_f32(epi, c.h(), true, md.cfg.rms_eps, (const float*)W, M, N, K, (float*)out, ldo, s);
+  if (md.ct == DT_F32) return gemm(DT_F32, epi, c.u(), W, M, N, K, out, ldo, s);
+  if (M > 64) return gemm_tokens(epi, c.u(), Wf, M, N, K, out, ldo, s);
+  const int S = short_wide(c, M, N, K, false);
+  if (S == 0) return gemm_tokens_short(epi, c.u(), Wf, M, N, K, out, ldo, s);
+  if (epi == EPI_SWIGLU && S == 1)
     return gemm_wide_reduce(epi, c.u(), nullptr, Wf, M, N, K, S, c.kpart(), c.wcnt(), out, nullptr, ldo, nullptr,
                             nullptr, nullptr, nullptr, nullptr, 0.f, s);
   hipError_t e = gemm_wide(c.u(), nullptr, Wf, M, N, K, S, c.kpart(), s);
@@ -364,21 +368,13 @@ static hipError_t layer_tokens(Ctx& c, int l, int M, const Segs& sg, hipStream_t
   const Cfg& m = md.cfg;
   const int d = m.d_model, F = m.d_ffn, dt = md.ct;
   const bool f32s = short_f32(md, M);  // the projections then normalise h themselves
-  const bool tiled = tiled_f16(md, M);
   if (!u_ready && !f32s) TRY(rmsnorm(dt, c.h(), M, d, m.rms_eps, c.u(), s));
   if (kv_fused) {  // the QKV GEMM's epilogue appends K/V (the token tables are the pass's)
     KvEpi kv{(const int64_t*)(c.ws + c.lay.tok_base), (const int32_t*)(c.ws + c.lay.tok_pos), c.kslab(l), c.vslab(l),
              c.rope(), d, m.head_dim};
     TRY(gemm_qkv_kv(c.u(), md.fqkv(l), M, d, c.qkv(), kv, s));
   } else {
-    if (f32s)
-      TRY(gemv_f32(EPI_STORE, c.h(), true, m.rms_eps, (const float*)md.wqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
-    else if (short_wide(md, M, 3 * d, d, false))
-      TRY(short_proj(c, EPI_STORE, md.fqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
-    else if (tiled)
-      TRY(gemm_tokens(EPI_STORE, c.u(), md.fqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
-    else
-      TRY(gemm(dt, EPI_STORE, c.u(), md.wqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
+    TRY(tokens_proj(c, EPI_STORE, md.wqkv(l), md.fqkv(l), M, 3 * d, d, c.qkv(), 3 * d, s));
     if (tables)  // each token's slot from the pass's tables (7B batch-64 extension: 19.05 -> 18.92 ms per step)
       TRY(kv_append_tab(c.qkv(), M, (const int64_t*)(c.ws + c.lay.tok_base), (const int32_t*)(c.ws + c.lay.tok_pos),
                         m.n_heads, m.head_dim, c.rope(), c.kslab(l), c.vslab(l), s));
@@ -389,14 +385,7 @@ static hipError_t layer_tokens(Ctx& c, int l, int M, const Segs& sg, hipStream_t
                    s));
   TRY(tokens_resid(c, c.o(), md.wo(l), md.fo(l), M, d, s, u_ready));
   if (!u_ready && !f32s) TRY(rmsnorm(dt, c.h(), M, d, m.rms_eps, c.u(), s));
-  if (f32s)
-    TRY(gemv_f32(EPI_SWIGLU, c.h(), true, m.rms_eps, (const float*)md.wgu(l), M, 2 * F, d, (float*)c.a(), F, s));
-  else if (short_wide(md, M, 2 * F, d, false))
-    TRY(short_proj(c, EPI_SWIGLU, md.fgu(l), M, 2 * F, d, c.a(), F, s));
-  else if (tiled)
-    TRY(gemm_tokens(EPI_SWIGLU, c.u(), md.fgu(l), M, 2 * F, d, c.a(), F, s));
-  else
-    TRY(gemm(dt, EPI_SWIGLU, c.u(), md.wgu(l), M, 2 * F, d, c.a(), F, s));
+  TRY(tokens_proj(c, EPI_SWIGLU, md.wgu(l), md.fgu(l), M, 2 * F, d, c.a(), F, s));
   TRY(tokens_resid(c, c.a(), md.wd(l), md.fd(l), M, F, s, u_ready));
   return hipSuccess;
 }

@@ -104,6 +104,7 @@ struct CtxLayout {
   int n_pages;        // pages in each layer's K (and V) pool
   size_t slab_layer;  // bytes of K (or V) for one layer: n_pages pages of 64 positions
   size_t kv, h, u, qkv, o, a, h_last, h_last16, h_last16lo, hlo, olo, alo, kpart, part, logits, rope, lens, meta, total;
+  size_t kpart_floats;  // floats of split-K partial sums kpart holds
   size_t order;  // the rows by decreasing length [B] int32 (decode attention dispatch order)
   size_t tok_base, tok_pos;  // a token pass's pool offsets [T] int64 and positions [T] int32 (K/V append)
   size_t ss;  // decode rows' sums of squares per 128 residual columns [B][d/128]
@@ -264,6 +265,7 @@ inline CtxLayout ctx_layout(const Cfg& c, int batch, int capacity, int pass_toke
                    decode_wsplit(2 * (int)F, (int)d, 64) * m * 2 * F, decode_wsplit((int)d, (int)F, 64) * m * d});
     kp = std::max({kp, tok_part_floats((int)d, (int)d, x.pass_tokens), tok_part_floats((int)d, (int)F, x.pass_tokens)});
   } else kp = std::max(kp, (size_t)std::max(f32_split((int)d, (int)d), f32_split((int)d, (int)F)) * std::min<size_t>(T, 64) * d);
+  x.kpart_floats = kp;
   x.kpart = o; o = align256(o + kp * 4);
   x.part = o; o = align256(o + B * (size_t)c.n_heads * x.max_splits * (c.head_dim + 2) * 4);
   x.logits = o; o = align256(o + B * (size_t)bins_padded(c) * 4);

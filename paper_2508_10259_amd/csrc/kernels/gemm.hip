@@ -74,7 +74,7 @@ constexpr int skinny_cpw() {
   return (RB + MB * (LO == 2 ? 2 : 1)) <= 2 ? 4 : ((RB + MB * (LO == 2 ? 2 : 1)) <= 4 ? 2 : 1);
 }
 
-template <int RB, int MB, int EPI, bool NRM, int LO>
+template <int RB, int MB, int EPI, bool NRM, int LO, bool FRAG>
 __global__ __launch_bounds__((64 * skinny_max_waves<RB, MB, LO>())) void k_gemm_skinny(SkinnyArgs a) {
   static_assert(!NRM || MB == 1, "the fused RMSNorm handles up to 16 tokens");
   static_assert(!NRM || EPI != EPI_PART, "the RMS statistic needs all of K");
@@ -100,7 +100,9 @@ __global__ __launch_bounds__((64 * skinny_max_waves<RB, MB, LO>())) void k_gemm_
 
   const f16* wrow[RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) wrow[rb] = a.W + (size_t)(n0 + rb * 16 + r) * K + g * 8;
+  for (int rb = 0; rb < RB; ++rb)
+    wrow[rb] = FRAG ? a.W + (size_t)(n0 + rb * 16) * K + lane * 8 : a.W + (size_t)(n0 + rb * 16 + r) * K + g * 8;
+  constexpr int WS = FRAG ? 16 : 1;  // a lane's weights of 32 columns on: 1 KB block on, or 64 bytes
   // B-operand rows of this lane: token mb*16 + r (LO == 1: token r & 7, hi for r < 8, lo above).
   // Columns of tokens >= M read token 0 instead of being masked (a masked load
   // costs a branch per load): they only feed output columns that are never
@@ -143,7 +145,7 @@ __global__ __launch_bounds__((64 * skinny_max_waves<RB, MB, LO>())) void k_gemm_
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) fw[j][rb][i] = ld_stream(wrow[rb] + kb + 32 * i);
+          for (int i = 0; i < 4; ++i) fw[j][rb][i] = ld_stream(wrow[rb] + (kb + 32 * i) * WS);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -244,7 +246,7 @@ __global__ __launch_bounds__((64 * skinny_max_waves<RB, MB, LO>())) void k_gemm_
   }
 }
 
-template <int RB, int MB, int EPI, bool NRM, int LO>
+template <int RB, int MB, int EPI, bool NRM, int LO, bool FRAG = false>
 static hipError_t launch_skinny(const SkinnyArgs& a, int N, hipStream_t s, int splits = 1) {
   // waves per workgroup: at most 64 KB of reduction LDS and at least one chunk
   // per wave; the 16-wave variant takes 16 only when every wave then gets a
@@ -255,7 +257,7 @@ static hipError_t launch_skinny(const SkinnyArgs& a, int N, hipStream_t s, int s
   while (nw > 1 && nw * RB * MB * 1024 > 65536) nw >>= 1;
   while (nw > 1 && nw > nchunks) nw >>= 1;
   const size_t lds = (size_t)nw * RB * MB * 1024 + (NRM ? (256 + 16) * 4 : 0);
-  hipLaunchKernelGGL((k_gemm_skinny<RB, MB, EPI, NRM, LO>), dim3(N / (RB * 16), splits), dim3(64 * nw), lds, s, a);
+  hipLaunchKernelGGL((k_gemm_skinny<RB, MB, EPI, NRM, LO, FRAG>), dim3(N / (RB * 16), splits), dim3(64 * nw), lds, s, a);
   return hipGetLastError();
 }
 
@@ -880,6 +882,30 @@ hipError_t gemm(int ct, int epi, const void* u, const void* W, int M, int N, int
     case EPI_STORE: return gemm_epi<EPI_STORE>(ct, u, W, M, N, K, out, ldo, s, ulo, o16, olo);
     case EPI_RESID: return gemm_epi<EPI_RESID>(ct, u, W, M, N, K, out, ldo, s, ulo, o16, olo);
     default: return gemm_epi<EPI_SWIGLU>(ct, u, W, M, N, K, out, ldo, s, ulo, o16, olo);
+  }
+}
+
+// Token passes: FRAG.  From row-major weights a wave's loads were 64-byte pieces of 16
+// rows (7B, 16 tokens: QKV 31.2 -> 22.8 us, gate|up 47.2 -> 39.3, O 12.1 -> 9.1, down
+// 27.2 -> 19.9; same sums).
+template <int EPI> static hipError_t tokens_short(const SkinnyArgs& a, int N, hipStream_t s) {
+  constexpr int RB = EPI == EPI_SWIGLU ? 2 : 1;
+  if (a.M <= 16) return launch_skinny<RB, 1, EPI, false, 0, true>(a, N, s);
+  if (a.M <= 32) return launch_skinny<RB, 2, EPI, false, 0, true>(a, N, s);
+  if (a.M <= 48) return launch_skinny<RB, 3, EPI, false, 0, true>(a, N, s);
+  return launch_skinny<RB, 4, EPI, false, 0, true>(a, N, s);
+}
+
+hipError_t gemm_tokens_short(int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo,
+                             hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  if (M > 64 || N % (epi == EPI_SWIGLU ? 32 : 16) != 0 || K % 128 != 0) return hipErrorInvalidValue;
+  const SkinnyArgs a{(const f16*)u, nullptr, 0.f, (const f16*)Wf, M, K, out, ldo, nullptr, nullptr};
+  switch (epi) {
+    case EPI_STORE: return tokens_short<EPI_STORE>(a, N, s);
+    case EPI_RESID: return tokens_short<EPI_RESID>(a, N, s);
+    case EPI_SWIGLU: return tokens_short<EPI_SWIGLU>(a, N, s);
+    default: return hipErrorInvalidValue;
   }
 }
 

@@ -135,6 +135,11 @@ hipError_t gemm_tokens(int epi, const void* u, const void* Wf, int M, int N, int
 hipError_t gemm_tokens_tile(int tile, int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo,
                             int splits, hipStream_t s, int segs = 1);
 
+// fp16 token passes of up to 64 tokens, Wf in fragment order (N a multiple of 16, 32 for
+// EPI_SWIGLU, K of 128): gemm() without the pair forms, bit for bit.
+hipError_t gemm_tokens_short(int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo,
+                             hipStream_t s);
+
 // Decode GEMV with the preceding RMSNorm fused (fp16, M <= 16), on the fp16
 // copy x = hhi (+ hlo, its rounding error, when non-NULL) of the residual rows:
 // y[m] = (W x[m]) / sqrt(mean(hhi[m]^2) + eps), followed by the epilogue as in

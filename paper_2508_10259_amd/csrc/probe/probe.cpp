@@ -64,6 +64,10 @@ int ams_probe_gemm_tokens_segs(int tile, const void* u, const void* Wf, int M, i
                                void* stream) {
   return (int)ams::gemm_tokens_tile(tile, ams::EPI_RESID, u, Wf, M, N, K, h, N, 1, (hipStream_t)stream, segs);
 }
+int ams_probe_gemm_tokens_short(int epi, const void* u, const void* Wf, int M, int N, int K, void* out, int ldo,
+                                void* stream) {
+  return (int)ams::gemm_tokens_short(epi, u, Wf, M, N, K, out, ldo, (hipStream_t)stream);
+}
 int ams_probe_tok_resid_splits(int M, int N, int K) { return ams::tok_resid_splits(M, N, K); }
 // out[0..3]: tile, splits, weight rows on it, tile of the rest (-1: none)
 void ams_probe_tok_plan(int M, int N, int K, int split, int32_t* out) {

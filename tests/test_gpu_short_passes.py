@@ -1,7 +1,7 @@
-"""fp16 token passes of at most 64 tokens on weights large enough for the wide GEMM (QKV and gate|up
-from 10 M weights, residual projections from 4 M), against the fp64 reference: builds and appends on
-both sides of the 16-token switch between the fused and the separate split-K reductions, and with a
-gate|up projection of one split (SwiGLU from registers) and of two."""
+"""fp16 token passes of at most 64 tokens on weights large enough for the wide GEMM (33 to 64
+tokens; QKV and gate|up from 10 M weights, residual projections from 4 M), against the fp64
+reference: builds and appends on both sides of its 32-token switch, and with a gate|up projection of
+one split (SwiGLU from registers) and of two."""
 import pytest
 
 from paper_2508_10259_amd import workload as W

@@ -120,3 +120,35 @@ def test_norms_same_bits(probe, d, splits):  # noqa: F811
         assert probe.ams_probe_resid_norm(_ptr(p), splits, M, d, _ptr(h), eps, _ptr(ur), _stream()) == 0
         out[M] = (un, ur, h)
         assert all(torch.equal(a, b[:M]) for a, b in zip(out[M], out[400])), M
+
+
+@pytest.mark.parametrize("M", [1, 8, 9, 16, 17, 32, 33, 48, 64])
+@pytest.mark.parametrize("N,K", [(96, 128), (416, 1152), (1024, 4096)])
+@pytest.mark.parametrize("epi", [EPI_STORE, EPI_RESID, EPI_SWIGLU])
+def test_tokens_short(probe, M, N, K, epi):  # noqa: F811
+    """Passes of up to 64 tokens against the exact product, and bit for bit the GEMV on row-major weights."""
+    import torch
+    log(f"tokens_short epi={epi} M={M} N={N} K={K}")
+    u, Wt = _rand((M, K), 121, M, K), _rand((N, K), 122, N, K, std=0.05)
+    ldo = N // 2 if epi == EPI_SWIGLU else N
+    h0 = W.random_gaussian((M, N), 123, M, dtype="f32")
+    dt = torch.float16 if epi == EPI_SWIGLU else torch.float32
+    a = torch.zeros((M, ldo), dtype=dt, device="cuda") if epi == EPI_SWIGLU else torch.from_numpy(h0.copy()).cuda()
+    b = a.clone()
+    ud = _dev(u, "f16")
+    wd, wf = _dev(Wt, "f16"), _dev(_frag32(Wt), "f16")
+    assert probe.ams_probe_gemm_tokens_short(epi, _ptr(ud), _ptr(wf), M, N, K, _ptr(a), ldo, _stream()) == 0
+    assert probe.ams_probe_gemm(2, epi, _ptr(ud), None, _ptr(wd), M, N, K, _ptr(b), ldo, None, None,
+                                _stream()) == 0
+    assert torch.equal(a, b)
+    y = _f(u, "f16") @ _f(Wt, "f16").T
+    if epi == EPI_SWIGLU:
+        g, up = _unpack_gu(y.T, N // 2)
+        y = (_silu(g) * up).T
+    elif epi == EPI_RESID:
+        y = y + h0
+    scale = max(1.0, float(np.max(np.abs(y))))
+    tol = max(2e-5 * scale * np.sqrt(K / 64), 2 ** -11 * scale if epi == EPI_SWIGLU else 0.0)
+    assert float(np.max(np.abs(a.double().cpu().numpy() - y))) <= tol
+    assert probe.ams_probe_gemm_tokens_short(epi, _ptr(ud), _ptr(wf), 65, N, K, _ptr(a), ldo, _stream()) != 0
+    assert probe.ams_probe_gemm_tokens_short(epi, _ptr(ud), _ptr(wf), M, N, K - 64, _ptr(a), ldo, _stream()) != 0
