@@ -27,6 +27,11 @@ static bool fused_norm(const Ctx& c, int rows) { return c.model->ct == DT_F16 &&
 // fp32 passes of up to 64 tokens run gemv_f32, which applies the RMSNorm itself.
 static bool short_f32(const Model& md, int M) { return md.ct == DT_F32 && M <= 64; }
 
+// K splits of a wide GEMM whose partial sums kpart holds.
+static int wide_splits(const Ctx& c, int M, int N, int K) {
+  return std::max(1, std::min(decode_wsplit(N, K, M), (int)(c.lay.kpart_floats / ((size_t)M * N))));
+}
+
 // K splits of a projection (N x K) of an fp16 token pass of 33 to 64 tokens that runs
 // the wide GEMM, 0 where it runs gemm_tokens_short: the wide GEMM from 10 M weights on
 // (4 M for the residual ones), where every strip of the short form would read the tokens
@@ -36,16 +41,23 @@ static bool short_f32(const Model& md, int M) { return md.ct == DT_F32 && M <= 6
 // 18.8; 32 tokens: 29.8 against 22.4).
 static int short_wide(const Ctx& c, int M, int N, int K, bool resid) {
   if (c.model->ct != DT_F16 || M <= 32 || M > 64 || (size_t)N * K < (resid ? 4000000u : 10000000u)) return 0;
-  const int S = decode_wsplit(N, K, M);
+  const int S = wide_splits(c, M, N, K);
   return (size_t)S * M * N <= c.lay.kpart_floats ? S : 0;
 }
 
 // h += x W^T of a short fp32 pass, K split over more workgroups for long rows.
 static hipError_t resid_f32(const Ctx& c, const void* x, const void* W, int M, int K, float* h, hipStream_t s) {
   const int d = c.model->cfg.d_model;
-  return gemv_f32(EPI_RESID, (const float*)x, false, 0.f, (const float*)W, M, d, K, h, d, s, f32_split(d, K), c.kpart(),
-                  c.wcnt());
+  int S = f32_split(d, K);
+  float* part = c.kpart();
+  if ((size_t)S * M * d > c.lay.kpart_floats) {
+    part = (float*)c.u();
+    S = std::min(S, 4);
+  }
+  return gemv_f32(EPI_RESID, (const float*)x, false, 0.f, (const float*)W, M, d, K, h, d, s, S, part,
+                  (unsigned*)(c.ws + c.lay.hlo));
 }
+
 
 // Above 8 rows the fp16 decode GEMVs use the wide GEMM (128 weight rows per
 // workgroup, activations staged in LDS) with split-K partial sums: at 16 rows
@@ -530,7 +542,7 @@ static hipError_t norm_proj(const Rows& g, int epi, const float* h, const void* 
       TRY(rmsnorm(md.ct, h, g.n, K, eps, g.u(), s, ulo));
     }
     if (wide) {  // partial sums of 128-row tiles, then the epilogue
-      const int splits = decode_wsplit(N, K, g.n);
+      const int splits = wide_splits(*g.c, g.n, N, K);
       if (epi == EPI_SWIGLU ? splits == 1 : !defer && wide_fused_reduce(g.n)) {
         TRY(gemm_wide_reduce(epi, g.u(), ulo, Wf, g.n, N, K, splits, g.c->kpart(), g.c->wcnt(), out, olo, ldo, nullptr,
                              nullptr, nullptr, nullptr, ss, eps, s));
@@ -562,7 +574,7 @@ static hipError_t resid_proj(const Rows& g, const void* x, const void* xlo, cons
   const Model& md = *c.model;
   const int d = md.cfg.d_model;
   if (wide_decode(c, g.n, d)) {
-    const int splits = decode_wsplit(d, K, g.n);
+    const int splits = wide_splits(c, g.n, d, K);
     void* o16 = ss ? g.u() : hhi;
     void* olo = ss ? g.hlo() : hlo;
     if (wide_fused_reduce(g.n))

@@ -108,7 +108,7 @@ struct CtxLayout {
   size_t order;  // the rows by decreasing length [B] int32 (decode attention dispatch order)
   size_t tok_base, tok_pos;  // a token pass's pool offsets [T] int64 and positions [T] int32 (K/V append)
   size_t ss;  // decode rows' sums of squares per 128 residual columns [B][d/128]
-  size_t wcnt;  // arrival counters of the split-K GEMMs' weight tiles (zero between launches)
+  size_t wcnt;  // arrival counters of the wide decode GEMM's weight tiles (zero between launches)
   // persistent decode (fp16, up to 8 rows): fp16 pairs [2][B][width] of h, the
   // attention output and the SwiGLU output, split-K partials, sync words
   size_t fx_hp, fx_op, fx_ap, fx_part, fx_sync;
@@ -160,6 +160,18 @@ inline int decode_wsplit(int N, int K, int M) {
   return std::max(1, std::min({(2 * wgs + tiles) / (2 * tiles), (K / 128) / 2, tiles < 8 ? 16 : 8}));
 }
 
+// K splits of a wide GEMM that the workspace of 9 to 64 rows has room for at least: the
+// smallest of 16 within 5% of the best ratio of work to rounds of 256 workgroups.
+inline int wide_room_splits(int N, int K) {
+  const int tiles = std::max(N / 128, 1), smax = std::max(1, std::min(16, (K / 128) / 4));
+  auto t = [&](int s) { return (double)((tiles * s + 255) / 256) / s; };
+  double best = t(1);
+  for (int s = 2; s <= smax; ++s) best = std::min(best, t(s));
+  int s = 1;
+  while (t(s) > 1.05 * best) ++s;
+  return s;
+}
+
 // Persistent decode (one launch per step) applies up to this many rows.
 constexpr int FUSED_MAX_ROWS = 8;
 // Split-K units of its O and down projections: at most this many.
@@ -200,6 +212,7 @@ inline int fused_split_attn(const Cfg& c, int rows, int capacity, int grid) {
 // one workgroup each): a strip's weights (64 K bytes) are kept to about 64 KB per
 // split while the splits' strips number at most 256, one per CU.  Merging the
 // splits costs a counter round trip (about 2 us), which shorter ranges do not repay.
+// At most 4 where their sums take the place of u and qkv (see ctx_layout).
 inline int f32_split(int N, int K) {
   return std::max(1, std::min(K / 1024, 256 / std::max(N / 16, 1)));
 }
@@ -247,24 +260,23 @@ inline CtxLayout ctx_layout(const Cfg& c, int batch, int capacity, int pass_toke
   x.hlo = o; o = align256(o + B * d * 2);
   x.olo = o; o = align256(o + B * d * 2);
   x.alo = o; o = align256(o + B * F * 2);
-  // split-K partial sums (fp16 compute): the decode GEMVs' (the narrow residual
-  // projections at up to 8 rows, every projection above 8 rows) and the token
-  // passes' residual projections at medium token counts
+  // split-K partial sums: the decode GEMVs' (the narrow residual projections at up
+  // to 8 rows, every projection above 8 rows) and the fp16 token passes' residual
+  // projections at medium token counts.  The launches take as many splits as fit here;
+  // fp32 residual projections may use u and qkv instead, which lie side by side, hold
+  // 4 T d floats and are read by nothing while such a projection runs, and keep their
+  // arrival counters in hlo, which only fp16 models use.
   size_t kp = 0;
   const size_t ks = std::max(decode_ksplit((int)d, (int)d), decode_ksplit((int)d, (int)F));
   if (ks > 1) kp = ks * B * d;
   if (batch > 8 && batch <= 64) {
     const size_t NB = bins_padded(c);
-    kp = std::max({kp, decode_wsplit(3 * (int)d, (int)d, 64) * B * 3 * d, decode_wsplit((int)d, (int)d, 64) * B * d,
-                   decode_wsplit(2 * (int)F, (int)d, 64) * B * 2 * F, decode_wsplit((int)d, (int)F, 64) * B * d,
-                   decode_wsplit((int)NB, (int)d, 64) * B * NB});
+    kp = std::max({kp, wide_room_splits(3 * (int)d, (int)d) * B * 3 * d, wide_room_splits((int)d, (int)d) * B * d,
+                   wide_room_splits(2 * (int)F, (int)d) * B * 2 * F, wide_room_splits((int)d, (int)F) * B * d,
+                   wide_room_splits((int)NB, (int)d) * B * NB});
   }
-  if (es == 2) {  // token passes of up to 64 tokens, and longer ones
-    const size_t m = std::min<size_t>(T, 64);
-    kp = std::max({kp, decode_wsplit(3 * (int)d, (int)d, 64) * m * 3 * d, decode_wsplit((int)d, (int)d, 64) * m * d,
-                   decode_wsplit(2 * (int)F, (int)d, 64) * m * 2 * F, decode_wsplit((int)d, (int)F, 64) * m * d});
+  if (es == 2)
     kp = std::max({kp, tok_part_floats((int)d, (int)d, x.pass_tokens), tok_part_floats((int)d, (int)F, x.pass_tokens)});
-  } else kp = std::max(kp, (size_t)std::max(f32_split((int)d, (int)d), f32_split((int)d, (int)F)) * std::min<size_t>(T, 64) * d);
   x.kpart_floats = kp;
   x.kpart = o; o = align256(o + kp * 4);
   x.part = o; o = align256(o + B * (size_t)c.n_heads * x.max_splits * (c.head_dim + 2) * 4);
@@ -293,7 +305,7 @@ inline CtxLayout ctx_layout(const Cfg& c, int batch, int capacity, int pass_toke
   x.hk_keys = o; o = align256(o + (share ? B * (size_t)x.ppr * 8 : 0));
   x.hk_rows = o; o = align256(o + (share ? 2 * B * 8 : 0));
   x.xfer = o; o = align256(o + B * 16);
-  x.wcnt = o; o = align256(o + std::max({3 * d / 128, 2 * F / 128, (size_t)bins_padded(c) / 128, d / 16}) * 4);
+  x.wcnt = o; o = align256(o + std::max({3 * d, 2 * F, (size_t)bins_padded(c), d}) / 128 * 4);
   x.total = o;
   return x;
 }

@@ -54,6 +54,19 @@ def test_status_strings(lib):
     assert lib.ams_status_str(99) == b"AMS_UNKNOWN"
 
 
+@pytest.mark.parametrize("dims,batch,capacity,room", [
+    ((32, 4096, 32, 11008, 1), 64, 768, 29281861376), ((4, 2048, 16, 5504, 1), 16, 704, 1051387648),
+    ((12, 1024, 16, 4096, 1), 8, 320, 275912192), ((32, 4096, 32, 11008, 1), 1, 320, 269076480),
+    ((4, 1024, 16, 4096, 0), 4, 512, 151439104),
+    ((2, 256, 4, 1024, 0), 1, 128, 1879552), ((2, 640, 10, 8192, 0), 64, 64, 245115648)])
+def test_context_fits_its_former_room(lib, dims, batch, capacity, room):
+    """Split counts adapt to the workspace and not the reverse: contexts fit buffers of the sizes
+    they had before the split rules were retuned."""
+    L, d, H, F, dtype = dims
+    c = _cfg(n_layers=L, d_model=d, n_heads=H, head_dim=d // H, d_ffn=F, vocab=2000, dtype=dtype)
+    assert 0 < lib.ams_ctx_workspace_bytes(C.byref(c), batch, capacity, 0) <= room
+
+
 def test_workspace_sizes(lib):
     c = _cfg()
     mb = lib.ams_model_workspace_bytes(C.byref(c))
