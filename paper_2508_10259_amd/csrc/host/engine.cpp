@@ -64,7 +64,9 @@ static hipError_t resid_f32(const Ctx& c, const void* x, const void* W, int M, i
 // of the 7B model it decodes 4% faster than the skinny GEMV with separate lo
 // fragments.
 static bool wide_decode(const Ctx& c, int rows, int N) {
-  return c.model->ct == DT_F16 && rows > 8 && rows <= 64 && N % 128 == 0;
+  const Cfg& m = c.model->cfg;  // (contexts of more than 64 rows may have no room for one split's sums)
+  return c.model->ct == DT_F16 && rows > 8 && rows <= 64 && N % 128 == 0 &&
+         (size_t)rows * std::max(3 * m.d_model, bins_padded(m)) <= c.lay.kpart_floats;
 }
 
 // On the wide path the RMSNorm of a projection input needs no kernel of its
@@ -695,12 +697,18 @@ static hipError_t enqueue_fused(Ctx& c, int A, int32_t* tok, float* logits, cons
   return hipSuccess;
 }
 
-// The greedy loop of a step over all rows.
+// The greedy loop of a step over all rows; the fp16 decode GEMVs take at most 64 at once.
 static hipError_t enqueue_decode(Ctx& c, int A, int32_t* tok, float* logits, const int32_t* forced, hipStream_t s,
                                  std::string& err) {
   if (c.fused_grid > 0) return enqueue_fused(c, A, tok, logits, forced, s, err);
-  const size_t ces = c.model->ct == DT_F16 ? 2 : 4;
-  return decode_rows(Rows{0, c.lay.batch, ces, &c}, A, tok, logits, forced, s, err);
+  const bool f16 = c.model->ct == DT_F16;
+  const int B = c.lay.batch, groups = f16 ? (B + 63) / 64 : 1;
+  for (int i = 0; i < groups; ++i) {
+    const int r0 = i * B / groups, r1 = (i + 1) * B / groups;
+    if (decode_rows(Rows{r0, r1 - r0, f16 ? (size_t)2 : 4, &c}, A, tok, logits, forced, s, err) != hipSuccess)
+      return hipErrorLaunchFailure;
+  }
+  return hipSuccess;
 }
 
 static bool graphs_enabled() {
