@@ -78,7 +78,7 @@ size_t ams_probe_tok_part_floats(int N, int K, int T) { return ams::tok_part_flo
 
 int ams_probe_gemm_big(int epi, const void* u, const void* W, int M, int N, int K, void* out, int ldo, int bn,
                        void* stream) {
-  const int tile = bn == 256 ? ams::TT_256x256 : bn == 128 ? ams::TT_256x128 : ams::TT_128x64;  // 192: three of 64
+  const int tile = bn == 256 ? ams::TT_256x256 : bn == 128 ? ams::TT_256x128 : ams::TT_128x64;
   Packed w(W, N, K, (hipStream_t)stream);
   return w.run([&] { return ams::gemm_tokens_tile(tile, epi, u, w.p, M, N, K, out, ldo, 1, w.s); });
 }
