@@ -286,7 +286,8 @@ static hipError_t skinny_dispatch(const SkinnyArgs& a, int N, hipStream_t s) {
 }
 
 // ----------------------------------------------------------------------------
-// wide decode GEMM: 16 < M <= 64 tokens (batched decode), split-K partial sums
+// wide GEMM: split-K partial sums of a batched decode's 9 to 64 rows and of token
+// passes of 33 to 64 tokens on large weights
 //
 // A workgroup owns 128 weight rows (8 waves x 16) and one K split.  Every
 // 128-wide K chunk of the activations (hi, and lo for the fp16 pair; all M
@@ -349,7 +350,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wide_rsrc(const void* p, uint3
 }
 
 // The reduction of one 128-column tile by the last of its splits to finish
-// (EPI_STORE / EPI_SWIGLU / EPI_RESID): every split's partial sums went out
+// (EPI_STORE / EPI_RESID): every split's partial sums went out
 // with device-scope stores, completed before the split counted itself in, so
 // the last arrival reads them all (device-scope loads: the XCDs' L2s are not
 // coherent with each other) and adds them in split order, the order the
@@ -409,50 +410,36 @@ __device__ void wide_reduce(const WideEpi& e, __amdgpu_buffer_rsrc_t pr, int S, 
     }
     return v;
   };
-  if constexpr (EPI == EPI_SWIGLU) {
-    // packed rows 32i + j (gate, j < 16) and 32i + 16 + j (up) give output column n0/2 + 16i + j
-    for (int x = tid; x < M * 16; x += blockDim.x) {
-      const int m = x >> 4, q = x & 15, i = q >> 2, j4 = (q & 3) * 4;
-      const float4 gt = sum4(m, n0 + 32 * i + j4), up = sum4(m, n0 + 32 * i + 16 + j4);
-      const float sc = rs[m];
-      const size_t o = (size_t)m * e.ldo + (n0 >> 1) + 16 * i + j4;
-      split16(silu(gt.x * sc) * (up.x * sc), (f16*)e.out, (f16*)e.olo, o);
-      split16(silu(gt.y * sc) * (up.y * sc), (f16*)e.out, (f16*)e.olo, o + 1);
-      split16(silu(gt.z * sc) * (up.z * sc), (f16*)e.out, (f16*)e.olo, o + 2);
-      split16(silu(gt.w * sc) * (up.w * sc), (f16*)e.out, (f16*)e.olo, o + 3);
-    }
-  } else {
-    // 32 threads (half a wave) per row, 4 columns each
-    for (int x = tid; x < ((M + 15) & ~15) * 32; x += blockDim.x) {
-      const int m = x >> 5, n = n0 + 4 * (x & 31);
-      const bool in = m < M;  // uniform over each half wave
-      float4 v = {0.f, 0.f, 0.f, 0.f};
-      if (in) v = sum4(m, n);
-      if constexpr (EPI == EPI_STORE) {
-        if (in) {
-          const float sc = rs[m];
-          *(float4*)((float*)e.out + (size_t)m * e.ldo + n) = float4{v.x * sc, v.y * sc, v.z * sc, v.w * sc};
-        }
-      } else {
-        float q = 0.f;
-        if (in) {
-          float4* hp = (float4*)(e.h + (size_t)m * N + n);
-          float4 hv = *hp;
-          hv.x += v.x; hv.y += v.y; hv.z += v.z; hv.w += v.w;
-          *hp = hv;
-          if (e.o16) {
-            const size_t o = (size_t)m * N + n;
-            split16(hv.x, (f16*)e.o16, (f16*)e.olo2, o);
-            split16(hv.y, (f16*)e.o16, (f16*)e.olo2, o + 1);
-            split16(hv.z, (f16*)e.o16, (f16*)e.olo2, o + 2);
-            split16(hv.w, (f16*)e.o16, (f16*)e.olo2, o + 3);
-          }
-          q = (hv.x * hv.x + hv.y * hv.y) + (hv.z * hv.z + hv.w * hv.w);
-        }
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
-        if (in && e.ss_out && (x & 31) == 0) e.ss_out[(size_t)m * (N / 128) + (n0 >> 7)] = q;
+  // 32 threads (half a wave) per row, 4 columns each
+  for (int x = tid; x < ((M + 15) & ~15) * 32; x += blockDim.x) {
+    const int m = x >> 5, n = n0 + 4 * (x & 31);
+    const bool in = m < M;  // uniform over each half wave
+    float4 v = {0.f, 0.f, 0.f, 0.f};
+    if (in) v = sum4(m, n);
+    if constexpr (EPI == EPI_STORE) {
+      if (in) {
+        const float sc = rs[m];
+        *(float4*)((float*)e.out + (size_t)m * e.ldo + n) = float4{v.x * sc, v.y * sc, v.z * sc, v.w * sc};
       }
+    } else {
+      float q = 0.f;
+      if (in) {
+        float4* hp = (float4*)(e.h + (size_t)m * N + n);
+        float4 hv = *hp;
+        hv.x += v.x; hv.y += v.y; hv.z += v.z; hv.w += v.w;
+        *hp = hv;
+        if (e.o16) {
+          const size_t o = (size_t)m * N + n;
+          split16(hv.x, (f16*)e.o16, (f16*)e.olo2, o);
+          split16(hv.y, (f16*)e.o16, (f16*)e.olo2, o + 1);
+          split16(hv.z, (f16*)e.o16, (f16*)e.olo2, o + 2);
+          split16(hv.w, (f16*)e.o16, (f16*)e.olo2, o + 3);
+        }
+        q = (hv.x * hv.x + hv.y * hv.y) + (hv.z * hv.z + hv.w * hv.w);
+      }
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+      if (in && e.ss_out && (x & 31) == 0) e.ss_out[(size_t)m * (N / 128) + (n0 >> 7)] = q;
     }
   }
 }
@@ -523,10 +510,8 @@ __global__ __launch_bounds__(512) void k_gemm_wide(const f16* __restrict__ xhi, 
   f32x4 acc[MB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // one split: the SwiGLU epilogue runs from registers (see the end)
   __shared__ float rs1[EPI == EPI_SWIGLU ? 64 : 1];
-  const bool direct = EPI == EPI_SWIGLU && S == 1;
-  if (direct) wide_rstd(ep.ss_in, M, K, ep.eps, rs1);
+  if constexpr (EPI == EPI_SWIGLU) wide_rstd(ep.ss_in, M, K, ep.eps, rs1);
 
   // one K chunk t: its MFMAs from stage t & 1 and weights w, then staging chunk
   // t+1, the activation loads of chunk t+2 and the weight loads of chunk t+WP
@@ -609,7 +594,7 @@ __global__ __launch_bounds__(512) void k_gemm_wide(const f16* __restrict__ xhi, 
       float* dst = part + ((size_t)sp * M + tok) * N + n0 + 4 * g;
       *(float4*)dst = float4{acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]};
     }
-  } else if (direct) {
+  } else if constexpr (EPI == EPI_SWIGLU) {  // one split: from registers
     // even waves hold gate rows, odd waves the up rows of the same 16 outputs: the up
     // values pass through the staging LDS, and the outputs leave without the partial
     // sums' trip through memory and without a second launch (7B gate|up, 16 rows: 37.6
@@ -679,10 +664,13 @@ static hipError_t wide_epi(const void* u, const void* ulo, const void* W, int M,
                            const WideEpi& ep, hipStream_t s) {
   const f16 *x = (const f16*)u, *xl = (const f16*)ulo, *w = (const f16*)W;
   if (!ulo) {
-    if (M <= 16) return launch_wide<1, 0, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
-    if (M <= 32) return launch_wide<2, 0, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
-    if (M <= 48) return launch_wide<3, 0, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
-    return launch_wide<4, 0, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
+    if constexpr (EPI == EPI_PART || EPI == EPI_SWIGLU) {
+      if (M <= 16) return launch_wide<1, 0, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
+      if (M <= 32) return launch_wide<2, 0, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
+      if (M <= 48) return launch_wide<3, 0, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
+      return launch_wide<4, 0, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
+    }
+    return hipErrorInvalidValue;  // the fused reductions serve the decode's pairs
   }
   if (M <= 16) return launch_wide<1, 2, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
   if (M <= 32) return launch_wide<2, 2, EPI>(x, xl, w, M, N, K, splits, part, ep, s);
@@ -713,7 +701,7 @@ hipError_t gemm_wide_reduce(int epi, const void* u, const void* ulo, const void*
       if (!out || ldo < N) return hipErrorInvalidValue;
       return wide_epi<EPI_STORE>(u, ulo, W, M, N, K, splits, part, ep, s);
     case EPI_SWIGLU:
-      if (!out || N % (2 * GU_BLOCK) != 0 || ldo < N / 2) return hipErrorInvalidValue;
+      if (!out || ldo < N / 2 || splits != 1) return hipErrorInvalidValue;
       return wide_epi<EPI_SWIGLU>(u, ulo, W, M, N, K, splits, part, ep, s);
     case EPI_RESID:
       if (!h || (olo2 && !o16)) return hipErrorInvalidValue;

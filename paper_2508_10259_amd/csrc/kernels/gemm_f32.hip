@@ -18,7 +18,7 @@ namespace ams {
 // owns a strip of 16 packed weight rows (32 for SwiGLU: 16 gate + 16 up) on the
 // M side of the MFMA, the tokens are its 1..4 column blocks, and up to 16 waves
 // split K in chunks of 64 and meet in LDS, so even a 1 MB projection has
-// thousands of loads in flight.  NRM: the input is the residual stream itself;
+// thousands of loads in flight.  NRM (STORE, SWIGLU): the input is the residual stream itself;
 // the sums of squares come from the activation fragments and 1/rms scales the
 // result, which saves the separate norm launch (4.5 us each).
 //
@@ -44,8 +44,9 @@ struct GemvF32Args {
 
 template <int MB> constexpr int gemv_f32_waves() { return MB == 1 ? 16 : 8; }
 
-template <int RB, int MB, int EPI, bool NRM>
+template <int RB, int MB, int EPI>
 __global__ __launch_bounds__((64 * gemv_f32_waves<MB>())) void k_gemv_f32(GemvF32Args a) {
+  constexpr bool NRM = EPI != EPI_RESID;
   extern __shared__ float red[];  // [nw][RB][MB][64 lanes][4], then (NRM) wsum[nw][MB*16], rstd[MB*16]
   __shared__ int last;
   const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
@@ -172,40 +173,41 @@ __global__ __launch_bounds__((64 * gemv_f32_waves<MB>())) void k_gemv_f32(GemvF3
   }
 }
 
-template <int RB, int MB, int EPI, bool NRM>
+template <int RB, int MB, int EPI>
 static hipError_t launch_gemv_f32(const GemvF32Args& a, int splits, hipStream_t s) {
   const int nch = (a.K >> 6) / splits;
   int nw = gemv_f32_waves<MB>();
   while (nw > 1 && nw > nch) nw >>= 1;  // at least one chunk per wave
-  const size_t lds = (size_t)nw * RB * MB * 1024 + (NRM ? (size_t)(nw + 1) * MB * 64 : 0);
-  hipLaunchKernelGGL((k_gemv_f32<RB, MB, EPI, NRM>), dim3(a.N / (RB * 16), splits), dim3(64 * nw), lds, s, a);
+  const size_t lds = (size_t)nw * RB * MB * 1024 + (EPI != EPI_RESID ? (size_t)(nw + 1) * MB * 64 : 0);
+  hipLaunchKernelGGL((k_gemv_f32<RB, MB, EPI>), dim3(a.N / (RB * 16), splits), dim3(64 * nw), lds, s, a);
   return hipGetLastError();
 }
 
-template <int EPI, bool NRM>
+template <int EPI>
 static hipError_t gemv_f32_m(const GemvF32Args& a, int splits, hipStream_t s) {
   constexpr int RB = EPI == EPI_SWIGLU ? 2 : 1;
-  if (a.M <= 16) return launch_gemv_f32<RB, 1, EPI, NRM>(a, splits, s);
-  if (a.M <= 32) return launch_gemv_f32<RB, 2, EPI, NRM>(a, splits, s);
-  return launch_gemv_f32<RB, 4, EPI, NRM>(a, splits, s);
+  if (a.M <= 16) return launch_gemv_f32<RB, 1, EPI>(a, splits, s);
+  if (a.M <= 32) return launch_gemv_f32<RB, 2, EPI>(a, splits, s);
+  return launch_gemv_f32<RB, 4, EPI>(a, splits, s);
 }
 
 hipError_t gemv_f32(int epi, const float* x, bool norm, float eps, const float* W, int M, int N, int K, float* out,
                     int ldo, hipStream_t s, int splits, float* part, unsigned* cnt) {
   if (M <= 0) return hipSuccess;
   if (M > 64 || K % 64 != 0 || N % (epi == EPI_SWIGLU ? 32 : 16) != 0) return hipErrorInvalidValue;
-  if (splits < 1 || splits > K / 64 || (splits > 1 && (epi != EPI_RESID || norm || !part || !cnt)))
+  if (norm != (epi != EPI_RESID) || splits < 1 || splits > K / 64 ||
+      (splits > 1 && (epi != EPI_RESID || !part || !cnt)))
     return hipErrorInvalidValue;
   const GemvF32Args a{x, W, eps, M, N, K, out, ldo, part, cnt};
   switch (epi) {
-    case EPI_STORE: return norm ? gemv_f32_m<EPI_STORE, true>(a, 1, s) : gemv_f32_m<EPI_STORE, false>(a, 1, s);
-    case EPI_RESID: return norm ? hipErrorInvalidValue : gemv_f32_m<EPI_RESID, false>(a, splits, s);
-    default: return norm ? gemv_f32_m<EPI_SWIGLU, true>(a, 1, s) : gemv_f32_m<EPI_SWIGLU, false>(a, 1, s);
+    case EPI_STORE: return gemv_f32_m<EPI_STORE>(a, 1, s);
+    case EPI_RESID: return gemv_f32_m<EPI_RESID>(a, splits, s);
+    default: return gemv_f32_m<EPI_SWIGLU>(a, 1, s);
   }
 }
 
 // ----------------------------------------------------------------------------
-// M > 64: MFMA tiles of T x T (T = 128 or 64), four waves of T/2 x T/2, K steps
+// Any M (the engine: more than 64): MFMA tiles of T x T (T = 128 or 64), four waves of T/2 x T/2, K steps
 // of BK staged through registers into double-buffered LDS.  Bound by the MFMA
 // rate: a step's arithmetic (2,048 cycles of a SIMD at T = 128) covers its
 // loads.  Rows are padded to 96 or 160 bytes, pitches at which the 16-byte
@@ -315,7 +317,6 @@ static hipError_t gemm_f32_epi(const float* u, const float* W, int M, int N, int
 
 hipError_t gemm_f32(int epi, const float* u, const float* W, int M, int N, int K, float* out, int ldo, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  if (M <= 64) return gemv_f32(epi, u, false, 0.f, W, M, N, K, out, ldo, s, 1, nullptr, nullptr);
   if (N % 64 != 0 || K % 32 != 0) return hipErrorInvalidValue;
   switch (epi) {
     case EPI_STORE: return gemm_f32_epi<EPI_STORE>(u, W, M, N, K, out, ldo, s);

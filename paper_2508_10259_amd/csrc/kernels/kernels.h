@@ -61,8 +61,8 @@ hipError_t gemm(int ct, int epi, const void* u, const void* W, int M, int N, int
                 int ldo, hipStream_t s, const void* ulo = nullptr, void* o16 = nullptr, void* olo = nullptr);
 
 // The fp32 forms (gemm() takes gemm_f32 for fp32 models).  gemv_f32: M <= 64, K a
-// multiple of 64; norm (STORE, SWIGLU): x is the residual stream and the result is
-// divided by the rms of its rows, sqrt(mean(x^2) + eps); splits > 1 (RESID): the
+// multiple of 64; norm (set for STORE and SWIGLU, not for RESID): x is the residual stream
+// and the result is divided by the rms of its rows, sqrt(mean(x^2) + eps); splits > 1 (RESID): the
 // K range in `splits` parts, part holding splits * M * N floats and cnt N / 16
 // counters, zero before the first call and left zero.
 hipError_t gemm_f32(int epi, const float* u, const float* W, int M, int N, int K, float* out, int ldo, hipStream_t s);
@@ -82,19 +82,20 @@ hipError_t gemm_part(const void* u, const void* ulo, const void* W, int M, int N
 // so a wave reads the A fragments of one MFMA step as 1 KB of contiguous memory.
 hipError_t frag_pack(const void* W, int N, int K, void* Wf, hipStream_t s);
 
-// Wide decode GEMM (fp16, 16 < M <= 64 typical, N a multiple of 128, W in
+// Wide GEMM (fp16, M <= 64, N a multiple of 128, W in
 // fragment order): the same partial sums as gemm_part, with 128 weight rows
 // per workgroup sharing LDS-staged activations.  The epilogue is one of the
 // part_* reductions.
 hipError_t gemm_wide(const void* u, const void* ulo, const void* W, int M, int N, int K, int splits, float* part,
                      hipStream_t s);
-// The wide decode GEMM (W in fragment order) with its reduction fused: each
+// The wide decode GEMM (W in fragment order; STORE and RESID: a pair as input) with its reduction fused: each
 // split stores its partial sums (part, splits * M * N floats) and the last
 // split of every 128-row weight tile to finish (per-tile counters, zero before
 // the first call, left zero) adds them in split order and applies the
 // epilogue, with the results of the part_* reductions:
 //   EPI_STORE : out[m*ldo + n] = y / rms_m        (rms_m from ss_in, or 1 when NULL)
-//   EPI_SWIGLU: out/olo[m*ldo + c] = silu(gate / rms_m) * (up / rms_m), fp16 pair
+//   EPI_SWIGLU: out/olo[m*ldo + c] = silu(gate / rms_m) * (up / rms_m), fp16 pair; one
+//               split only, from registers
 //   EPI_RESID : h[m][n] += y, the fp16 pair (o16, olo2) of the new rows when
 //               o16 is non-NULL, and the sums of squares of the new rows per 128
 //               columns in ss_out[m][n / 128] when non-NULL

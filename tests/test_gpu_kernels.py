@@ -932,11 +932,11 @@ def test_gemm_wide(probe, M, N, K, splits, pair):
 
 @pytest.mark.parametrize("M", [5, 33, 64])
 @pytest.mark.parametrize("N,K,splits", [(256, 1024, 1), (512, 4096, 8), (1152, 1408, 4), (2048, 1024, 3),
-                                        (256, 2048, 16)])
+                                        (256, 2048, 16), (1152, 1408, 1)])
 def test_gemm_wide_reduce(probe, M, N, K, splits):
     """The wide decode GEMM with its reduction fused (the last split of each 128-row tile adds
-    the partial sums in split order): store, SwiGLU and residual results equal those of the
-    separate reduction kernels bit for bit, the residual's sums of squares per 128 columns
+    the partial sums in split order; SwiGLU of one split from registers): results equal those of
+    the separate reduction kernels bit for bit, the residual's sums of squares per 128 columns
     match the new rows, the RMSNorm scale from given sums of squares matches the separate
     scaled reductions (or the closed form where they do not take the shape), and the tile
     counters are back at zero, so a second call gives the same results."""
@@ -979,18 +979,24 @@ def test_gemm_wide_reduce(probe, M, N, K, splits):
         assert torch.equal(out, ref_n)
     want = ref.cpu().numpy().astype(np.float64) * rstd
     assert float(np.max(np.abs(out.cpu().numpy() - want))) <= 1e-6 * max(1.0, float(np.max(np.abs(want))))
-    # SwiGLU (fp16 pair out)
-    a = torch.zeros((M, N // 2), dtype=torch.float16, device="cuda")
-    alo = torch.zeros_like(a)
-    assert probe.ams_probe_part_swiglu(_ptr(part), splits, M, N, _ptr(a), _ptr(alo), _stream()) == 0
-    a2, alo2 = torch.full_like(a, float("nan")), torch.full_like(alo, float("nan"))
-    fused(2, out=a2, olo=alo2, ldo=N // 2)
-    assert torch.equal(a, a2) and torch.equal(alo, alo2)
-    if (N // 2) % 256 == 0 and K % 256 == 0:
-        assert probe.ams_probe_part_swiglu_norm(_ptr(part), splits, M, N, _ptr(a), _ptr(alo), _ptr(ss_in), K, f,
-                                                _stream()) == 0
-        fused(2, out=a2, olo=alo2, ldo=N // 2, ss=ss_in)
+    # SwiGLU (fp16 pair out), of one split: more go through the separate reduction
+    if splits == 1:
+        a = torch.zeros((M, N // 2), dtype=torch.float16, device="cuda")
+        alo = torch.zeros_like(a)
+        assert probe.ams_probe_part_swiglu(_ptr(part), splits, M, N, _ptr(a), _ptr(alo), _stream()) == 0
+        a2, alo2 = torch.full_like(a, float("nan")), torch.full_like(alo, float("nan"))
+        fused(2, out=a2, olo=alo2, ldo=N // 2)
         assert torch.equal(a, a2) and torch.equal(alo, alo2)
+        if (N // 2) % 256 == 0 and K % 256 == 0:
+            assert probe.ams_probe_part_swiglu_norm(_ptr(part), splits, M, N, _ptr(a), _ptr(alo), _ptr(ss_in), K, f,
+                                                    _stream()) == 0
+            fused(2, out=a2, olo=alo2, ldo=N // 2, ss=ss_in)
+            assert torch.equal(a, a2) and torch.equal(alo, alo2)
+    else:
+        spare = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        assert probe.ams_probe_gemm_wide_reduce(2, _ptr(ud), _ptr(ulod), _ptr(Wd), M, N, K, splits, _ptr(part2),
+                                                _ptr(cnt), _ptr(spare), None, N // 2, None, None, None, None, None, f,
+                                                _stream()) != 0
     # residual with the fp16 pair and the sums of squares per 128 columns
     h0 = torch.from_numpy(W.random_gaussian((M, N), 83, M, dtype="f32")).cuda()
     h, o16, olo = h0.clone(), torch.zeros((M, N), dtype=torch.float16, device="cuda"), None
