@@ -47,7 +47,7 @@ template <int MB> constexpr int gemv_f32_waves() { return MB == 1 ? 16 : 8; }
 template <int RB, int MB, int EPI>
 __global__ __launch_bounds__((64 * gemv_f32_waves<MB>())) void k_gemv_f32(GemvF32Args a) {
   constexpr bool NRM = EPI != EPI_RESID;
-  extern __shared__ float red[];  // [nw][RB][MB][64 lanes][4], then (NRM) wsum[nw][MB*16], rstd[MB*16]
+  extern __shared__ __attribute__((aligned(16))) float red[];  // [nw][RB][MB][64 lanes][4], then (NRM) wsum[nw][MB*16], rstd[MB*16]
   __shared__ int last;
   const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
