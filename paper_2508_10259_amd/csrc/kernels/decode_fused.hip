@@ -89,7 +89,7 @@ constexpr unsigned SPIN_LIMIT = 1u << 22;   // polls (about a second or more) be
 
 constexpr int FUSED_X_CHUNKS = 32;  // inputs of up to 4,096: 128 KB
 
-struct FusedSmem {
+struct alignas(16) FusedSmem {
   float red[8 * 2 * 256];  // [wave][rb][lane][4] GEMV partial sums
   float wsum[8 * 16];      // [wave][token] RMS statistic partials
   float am[8], al[8];      // attention: per-wave max and sum
@@ -97,8 +97,11 @@ struct FusedSmem {
   int tok[8];              // feed: argmax per row
   int last;                // split-K: this workgroup finishes the strip
   int stop;                // a barrier wait timed out somewhere
-  // activation fragments of a phase whose units all read the same input
-  // ([chunk][step][lane]; every wave stages and reads its own chunks)
+};
+// With X also the activation fragments of a phase whose units all read the same
+// input ([chunk][step][lane]; every wave stages and reads its own chunks).
+template <bool X> struct FusedSmemX : FusedSmem {};
+template <> struct FusedSmemX<true> : FusedSmem {
   uint4 x[FUSED_X_CHUNKS * 4 * 64];
 };
 
@@ -311,7 +314,7 @@ __device__ __forceinline__ void gemv_unit(const f16* __restrict__ W, int K, int 
 // 16.16 -> 15.79 ms per step).  W of the first two batches is in pf.
 template <int RB>
 __device__ __forceinline__ void gemv_unit_x(const f16* __restrict__ W, int K, int n0, Rsrc xr, uint32_t lo_off, int M,
-                                            FusedSmem& sm, Prefetch& pf, bool first, int nxt) {
+                                            FusedSmemX<true>& sm, Prefetch& pf, bool first, int nxt) {
   constexpr int CB = GB<RB>::CB;
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   int w0, w1;
@@ -409,7 +412,7 @@ __device__ __forceinline__ const f16* layer_w(const f16* base, size_t stride, in
 // (sc1); j_head >= 0 (the head) also writes the caller's out_logits for bins < n_bins.
 template <bool XL>
 __device__ void phase_store(const FusedArgs& a, const f16* W, int N, int K, Rsrc xr, uint32_t lo_off, Rsrc outr,
-                            int ldo, int j_head, FusedSmem& sm, Prefetch& pf) {
+                            int ldo, int j_head, FusedSmemX<XL>& sm, Prefetch& pf) {
   const int units = N / 16, G = gridDim.x;
   for (int u = blockIdx.x; u < units; u += G) {
     if constexpr (XL)
@@ -436,7 +439,7 @@ __device__ __forceinline__ void prefetch_store(const f16* W, int N, int K, Prefe
 
 // a = silu(gate) * up of the packed gate|up rows (32-row units), as an fp16 pair.
 template <bool XL>
-__device__ void phase_swiglu(const FusedArgs& a, const f16* W, Rsrc xr, uint32_t lo_off, FusedSmem& sm,
+__device__ void phase_swiglu(const FusedArgs& a, const f16* W, Rsrc xr, uint32_t lo_off, FusedSmemX<XL>& sm,
                              Prefetch& pf) {
   const int F = a.F, units = (2 * F) / 32;
   const Rsrc apr = rsrc(a.ap, (uint32_t)(2 * a.M * F * 2));
@@ -840,7 +843,7 @@ __device__ void phase_feed(const FusedArgs& a, int j, bool feed, FusedSmem& sm) 
 // XL: d is at most 128 FUSED_X_CHUNKS, the phases that read h keep it in LDS
 template <int DH, bool XL>
 __global__ __launch_bounds__(512) void k_decode_fused(FusedArgs a) {
-  __shared__ FusedSmem sm;
+  __shared__ FusedSmemX<XL> sm;
   if (threadIdx.x == 0) sm.stop = 0;
   __syncthreads();
   const int d = a.d, M = a.M;
