@@ -354,9 +354,15 @@ __global__ __launch_bounds__(64 * WM * WN) void k_tok_pipe(const f16* __restrict
 
 // ----------------------------------------------------------------------------
 
+template <typename F> static hipError_t lds_limit(F* kernel, int bytes) {
+  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
 template <int EPI, int DH = 128>
 static hipError_t launch_pp(const f16* u, const f16* W, int M, int N, int K, void* out, int ldo, int splits,
                             const KvEpi& kv, hipStream_t s) {
+  static const hipError_t lim = lds_limit(k_tok_pp<EPI, DH>, PP_SLOTS * PP_SLOT);
+  if (lim != hipSuccess) return lim;
   hipLaunchKernelGGL((k_tok_pp<EPI, DH>), dim3((N / 256) * ((M + 255) / 256), splits), dim3(512), PP_SLOTS * PP_SLOT, s,
                      u, W, M, N, K, out, ldo, kv);
   return hipGetLastError();
@@ -366,6 +372,8 @@ template <int EPI, int BM, int BN, int WM, int WN, int NST, bool SEG>
 static hipError_t launch_pipe(const f16* u, const f16* W, int M, int N, int K, void* out, int ldo, int splits,
                               int segs, hipStream_t s) {
   constexpr int LDS = NST * (BM + BN) * 128;
+  static const hipError_t lim = lds_limit(k_tok_pipe<EPI, BM, BN, WM, WN, NST, SEG>, LDS);
+  if (lim != hipSuccess) return lim;
   hipLaunchKernelGGL((k_tok_pipe<EPI, BM, BN, WM, WN, NST, SEG>), dim3((N / BN) * ((M + BM - 1) / BM), splits),
                      dim3(64 * WM * WN), LDS, s, u, W, M, N, K, out, ldo, segs);
   return hipGetLastError();
