@@ -16,6 +16,7 @@
 //  * k_tok_pipe: smaller tiles with one to five K steps of loads in flight, for
 //    passes whose 256 x 256 tiles would leave CUs idle.  Bound by the latency and
 //    rate of the operand loads.
+#include <atomic>
 #include <type_traits>
 
 #include "common.h"
@@ -354,14 +355,23 @@ __global__ __launch_bounds__(64 * WM * WN) void k_tok_pipe(const f16* __restrict
 
 // ----------------------------------------------------------------------------
 
-template <typename F> static hipError_t lds_limit(F* kernel, int bytes) {
-  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+// Allows `kernel` `bytes` of dynamic LDS on the current device, once per device (done: a bit each).
+static hipError_t lds_limit(std::atomic<uint64_t>& done, const void* kernel, int bytes) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+  if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+  return e;
 }
 
 template <int EPI, int DH = 128>
 static hipError_t launch_pp(const f16* u, const f16* W, int M, int N, int K, void* out, int ldo, int splits,
                             const KvEpi& kv, hipStream_t s) {
-  static const hipError_t lim = lds_limit(k_tok_pp<EPI, DH>, PP_SLOTS * PP_SLOT);
+  static std::atomic<uint64_t> done{0};
+  const hipError_t lim = lds_limit(done, (const void*)k_tok_pp<EPI, DH>, PP_SLOTS * PP_SLOT);
   if (lim != hipSuccess) return lim;
   hipLaunchKernelGGL((k_tok_pp<EPI, DH>), dim3((N / 256) * ((M + 255) / 256), splits), dim3(512), PP_SLOTS * PP_SLOT, s,
                      u, W, M, N, K, out, ldo, kv);
@@ -372,7 +382,8 @@ template <int EPI, int BM, int BN, int WM, int WN, int NST, bool SEG>
 static hipError_t launch_pipe(const f16* u, const f16* W, int M, int N, int K, void* out, int ldo, int splits,
                               int segs, hipStream_t s) {
   constexpr int LDS = NST * (BM + BN) * 128;
-  static const hipError_t lim = lds_limit(k_tok_pipe<EPI, BM, BN, WM, WN, NST, SEG>, LDS);
+  static std::atomic<uint64_t> done{0};
+  const hipError_t lim = lds_limit(done, (const void*)k_tok_pipe<EPI, BM, BN, WM, WN, NST, SEG>, LDS);
   if (lim != hipSuccess) return lim;
   hipLaunchKernelGGL((k_tok_pipe<EPI, BM, BN, WM, WN, NST, SEG>), dim3((N / BN) * ((M + BM - 1) / BM), splits),
                      dim3(64 * WM * WN), LDS, s, u, W, M, N, K, out, ldo, segs);
