@@ -74,10 +74,9 @@ static bool wide_decode(const Ctx& c, int rows, int N) {
 // of h in (u, hlo) and its sums of squares per 128 columns, and the
 // projection's reduction divides its rows by rms.
 // Up to 16 rows the wide GEMM reduces its split-K partial sums in each tile's
-// last split instead of a separate kernel: measured on the 7B decoder at 16
-// rows, O 14.0 -> 12.6 us, down 23.6 -> 22.1 us, gate|up 41.0 -> 39.7 us; at 64
-// rows the O and down projections' 32 tiles would reduce on 32 CUs, 1-5 us
-// slower per projection.
+// last split instead of a separate kernel (not for SwiGLU): measured on the 7B
+// decoder at 16 rows, O 14.0 -> 12.6 us, down 23.6 -> 22.1 us; at 64 rows the O and
+// down projections' 32 tiles would reduce on 32 CUs, 1-5 us slower per projection.
 static bool wide_fused_reduce(int rows) { return rows <= 16; }
 
 static bool merge_norm(const Ctx& c, int rows) {

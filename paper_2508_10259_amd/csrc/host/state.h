@@ -15,9 +15,8 @@
 #include <unordered_map>
 #include <vector>
 
-#include "gemm_plan.h"
-
 #include "fused_limits.h"
+#include "gemm_plan.h"
 
 namespace ams {
 
@@ -66,8 +65,9 @@ inline int bins_padded(const Cfg& c) { return (c.n_bins + 63) / 64 * 64; }
 struct ModelLayout {
   size_t wqkv, wo, wgu, wd, head_bins, bin_embed, total;
   size_t per_layer_qkv, per_layer_o, per_layer_gu, per_layer_d;  // bytes per layer
-  // fp16 compute: a second copy of the decode-pass matrices in MFMA fragment
-  // order (frag_pack), same per-layer strides; 0 / unused for fp32 models
+  // fp16 compute: a second copy of the matrices in MFMA fragment order (frag_pack),
+  // which token passes and most decode passes read; same per-layer strides; 0 /
+  // unused for fp32 models
   size_t fqkv, fo, fgu, fd, fhead;
 };
 

@@ -1,6 +1,8 @@
 // Projection and feed-forward GEMMs: y = u W^T with fused epilogues.
 //
-//  * k_gemm_skinny  (fp16, M <= 64 tokens: the per-action decode pass).  HBM
+//  * k_gemm_skinny  (fp16, M <= 64 tokens: the per-action decode pass of up to 8
+//    rows outside the persistent kernel, and, on fragment-ordered weights, token passes
+//    but those of 33 to 64 tokens on large weights).  HBM
 //    bound on the weights: every weight byte is read exactly once.  A
 //    workgroup owns a strip of 16 (or 32 for SwiGLU: 16 gate + 16 up) packed weight rows; its
 //    waves split K in chunks of 128 and run v_mfma_f32_16x16x32_f16 with the
@@ -10,7 +12,7 @@
 //    SiLU-gate) runs on the reduced values.  Up to 16 tokens it can also
 //    apply the preceding RMSNorm itself (gemv_rmsnorm).  RMSNorm gains are
 //    folded into the packed weights, so every GEMM consumes h / rms(h).
-//  * k_gemm_wide    (fp16, batched decode of 9 to 64 rows).
+//  * k_gemm_wide    (fp16, batched decode of 9 to 64 rows, those token passes).
 //  Longer token passes: gemm_tokens.hip.
 //  fp32 models: gemm_f32.hip, same epilogues.
 #include "common.h"
@@ -449,7 +451,7 @@ __device__ void wide_reduce(const WideEpi& e, __amdgpu_buffer_rsrc_t pr, int S, 
 // more fragments a wave keeps two weight chunks in flight instead of three,
 // which holds it at 120 VGPRs (four waves per SIMD).  On the 7B shapes at 64
 // rows: gate|up 54.0 -> 50.8 us, QKV 32.7 -> 31.6 us, down 29.3 -> 25.5 us.
-// The reduction fused into the last split (EPI_STORE / _SWIGLU / _RESID)
+// The reduction fused into the last split (EPI_STORE / _RESID)
 // measured 1-2 us faster per residual projection than GEMM + reduction kernel at
 // 16 rows and 1-5 us slower at 64, where the O and down projections' 32 tiles
 // then reduce on 32 CUs; the engine uses it up to 16 rows.  For SwiGLU with
