@@ -239,8 +239,8 @@ __global__ __launch_bounds__(512) void k_tok_pp(const f16* __restrict__ u, const
 // stage of the step before is read out, and the loads NST - 1 steps ahead go into
 // it.  With one step prefetched into registers (128 x 128 tiles) a step cost a
 // whole memory round trip, 1.2 us, whatever its size.  Measured on the 7B
-// shapes: 128 tokens QKV 82 -> 34 us, gate|up 82 -> 45 us; 288 tokens QKV 73 -> 49;
-// 600 tokens QKV 89 -> 68 us, gate|up 180 -> 130 us, O 45 -> 30, down 100 -> 65.
+// shapes: 128 tokens QKV 82 -> 33 us, gate|up 82 -> 49 us; 288 tokens QKV 73 -> 51;
+// 600 tokens QKV 89 -> 72 us, down (six ranges, without their reduction) 100 -> 73.
 // The 128 x 64 tile and the two 128 x 128 workgroups of a CU have eight waves of 32
 // x 32 and 64 x 32: four left a SIMD one wave, which waited for the same stage as the
 // others (QKV of the 7B width at 128 tokens 34.0 -> 31.9 us, 30.9 -> 28.5 at 72; 288
